@@ -43,14 +43,14 @@ FP64_VECTOR_PEAK_TFLOPS = 78.6
 # MI355X published HBM3E bandwidth.
 HBM_PEAK_GBPS = 8000.0
 
-# FP64 FLOPs per integrand evaluation as the rule kernel implements it:
-# counted from the compiled corner-sweep loop of the one-lane-per-region rule
-# kernel at d = 8 (the loop that evaluates 256 of the 401 nodes of a region),
-# FMA = 2, ADD/MUL/RCP = 1, per corner: the amortized chain combinations of
-# per-coordinate terms, the outer function (exp / cos / reciprocal / powers)
-# and the compensated accumulation.  Cross-checked against the
-# SQ_INSTS_VALU_*_F64 counters (profiles/).
-FLOPS_PER_EVAL = {1: 42.75, 2: 7.0, 3: 16.8125, 4: 32.5, 5: 32.75, 6: 32.5, 7: 8.5}
+# FP64 FLOPs per integrand evaluation as the rule kernel implements it: the
+# corner sweep of the one-lane-per-region kernel at d = 8 (256 of a region's 401
+# nodes), FMA = 2, ADD/MUL/RCP = 1, per corner: its share of the tables of
+# partial products (or of the chain additions), the outer function where a node
+# has one (corner peak, polynomial) and the accumulation.  A factored family's
+# node is one multiply-add (rotations: two); forming its factors once per region
+# (56 exponentials or 24 sine-cosine pairs at d = 8) is not counted.
+FLOPS_PER_EVAL = {1: 5.45, 2: 2.31, 3: 16.8125, 4: 2.31, 5: 2.31, 6: 2.31, 7: 8.5}
 
 # HBM traffic of the rule kernel, per launch, measured with rocprofv3 --pmc
 # (FETCH_SIZE and WRITE_SIZE, each scaled by what the counter reads for a
@@ -59,8 +59,8 @@ FLOPS_PER_EVAL = {1: 42.75, 2: 7.0, 3: 16.8125, 4: 32.5, 5: 32.75, 6: 32.5, 7: 8
 # from; the figure is reported only while those sources are unchanged.
 TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "rule_kernel_d8_suite_counters.md")
 RULE_SOURCES = [os.path.join(ROOT, "paper_2511_01573_amd", "csrc", f)
-                for f in ("gm_rule.hip", "gm_corner.hpp", "gm_family.hpp", "gm_common.hpp",
-                          "gm_math.hpp", "gm_api.hip")]
+                for f in ("gm_rule.hip", "gm_factor.hip", "gm_nodes.hpp", "gm_corner.hpp",
+                          "gm_family.hpp", "gm_common.hpp", "gm_math.hpp", "gm_api.hip")]
 
 
 def parse():

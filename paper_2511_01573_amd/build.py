@@ -29,14 +29,17 @@ FLAGS = ["-O3", "-std=c++17", f"--offload-arch={ARCH}", "-ffp-contract=off", "-f
 FAMILIES = range(1, 8)
 # translation units compiled once per integrand family (template-heavy kernels)
 PER_FAMILY = ("gm_rule", "gm_rule9", "gm_adjoint", "gm_gk")
+# ... and those compiled once per factored kernel family (gm_common.hpp kOscF ..)
+PER_FACTOR = ("gm_factor", "gm_factor9")
+FACTOR_FAMILIES = range(8, 13)
 
 
 def _units():
     units = []
     for src in sorted(glob.glob(os.path.join(CSRC, "*.hip"))):
         name = os.path.splitext(os.path.basename(src))[0]
-        if name in PER_FAMILY:
-            for f in FAMILIES:
+        if name in PER_FAMILY or name in PER_FACTOR:
+            for f in (FAMILIES if name in PER_FAMILY else FACTOR_FAMILIES):
                 units.append((src, os.path.join(BUILD, f"{name}_f{f}.o"),
                               [f"-DGM_RULE_FAMILY={f}", f"-DGM_FAMILY={f}"]))
         else:

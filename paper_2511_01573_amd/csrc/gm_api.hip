@@ -724,13 +724,19 @@ int check_bounds(int rc) {
   {#name " f3", gm_check_poll_##name##_f3}, {#name " f4", gm_check_poll_##name##_f4}, \
   {#name " f5", gm_check_poll_##name##_f5}, {#name " f6", gm_check_poll_##name##_f6}, \
   {#name " f7", gm_check_poll_##name##_f7}
+#define GM_POLL_FACTOR(name)                                                              \
+  {#name " f8", gm_check_poll_##name##_f8}, {#name " f9", gm_check_poll_##name##_f9},     \
+  {#name " f10", gm_check_poll_##name##_f10}, {#name " f11", gm_check_poll_##name##_f11}, \
+  {#name " f12", gm_check_poll_##name##_f12}
   static const struct {
     const char* name;
     PollFn fn;
   } units[] = {{"api", gm_check_poll_api}, {"batch", gm_check_poll_batch},
                {"grad", gm_check_poll_grad}, GM_POLL_F(rule), GM_POLL_F(rule9),
-               GM_POLL_F(adjoint), GM_POLL_F(gk)};
+               GM_POLL_F(adjoint), GM_POLL_F(gk), GM_POLL_FACTOR(factor),
+               GM_POLL_FACTOR(factor9)};
 #undef GM_POLL_F
+#undef GM_POLL_FACTOR
   std::string first;
   unsigned long long total = 0;
   for (const auto& u : units) {
@@ -888,6 +894,43 @@ int validate(int fam, const double* params, int d, const double* lo, const doubl
   return GM_OK;
 }
 
+// The kernel family of integrand fam on [lo, hi]: the factored one (gm_nodes.hpp)
+// where the family has it and the parameters allow.  The product families need
+// every partial product to stay in the range of a double: the axes' largest
+// |log factor| add up to at most 500 (e^708 is the end).  Beyond it a partial
+// product could overflow or vanish although the integrand does not (a C0
+// integrand with large negative a_j), and node values below e^-500 are no more
+// accurate than the rounding of their exponent, which only the definition's
+// order of summation reproduces: those run in chain form.  The seeded families
+// stay below 100 and the paper's f2 below 16 per axis; its f4 (a = 25, u = 1/2)
+// passes the line from d = 4 on.  The rotations of the oscillatory family have
+// no such limit.
+int kernel_family(int fam, int d, const double* params, const double* lo, const double* hi) {
+  if (d < kFactorMinDim) return fam;
+  if (fam == kOsc) return kOscF;
+  if (fam != kProductPeak && fam != kGaussian && fam != kC0 && fam != kDiscontinuous) return fam;
+  double span = 0.0;
+  for (int j = 0; j < d; ++j) {
+    const double a = params[j], u = params[d + j];
+    const double far = std::max(std::fabs(lo[j] - u), std::fabs(hi[j] - u));
+    if (fam == kProductPeak) {  // the factor lies between 1 / (a^-2 + far^2) and a^2
+      const double inv_a2 = 1.0 / (a * a);
+      span += std::max(std::fabs(std::log(inv_a2)), std::fabs(std::log(inv_a2 + far * far)));
+    } else if (fam == kGaussian) {
+      span += (a * far) * (a * far);
+    } else if (fam == kC0) {
+      span += std::fabs(a) * far;
+    } else {
+      span += std::fabs(a) * std::max(std::fabs(lo[j]), std::fabs(hi[j]));
+    }
+  }
+  if (!(span <= 500.0)) return fam;  // (NaN: the chain form)
+  return fam == kProductPeak ? kProductPeakF
+         : fam == kGaussian  ? kGaussianF
+         : fam == kC0        ? kC0F
+                             : kDiscontinuousF;
+}
+
 int init_cells_log2(int d) { return g_opt.init_log2 / d; }
 
 RuleKernelFn rule_kernel(int d, int fam, int log2l, bool batch) {
@@ -899,6 +942,11 @@ RuleKernelFn rule_kernel(int d, int fam, int log2l, bool batch) {
     case 5: return rule_kernel_f5(d, log2l, batch);
     case 6: return rule_kernel_f6(d, log2l, batch);
     case 7: return rule_kernel_f7(d, log2l, batch);
+    case kOscF: return factor_kernel_f8(d, log2l, batch);
+    case kProductPeakF: return factor_kernel_f9(d, log2l, batch);
+    case kGaussianF: return factor_kernel_f10(d, log2l, batch);
+    case kC0F: return factor_kernel_f11(d, log2l, batch);
+    case kDiscontinuousF: return factor_kernel_f12(d, log2l, batch);
     default: return nullptr;
   }
 }
@@ -925,6 +973,11 @@ RuleKernelFn r9_kernel(int d, int fam, bool batch, bool wide) {
     case 5: return rule9_kernel_f5(d, batch, wide);
     case 6: return rule9_kernel_f6(d, batch, wide);
     case 7: return rule9_kernel_f7(d, batch, wide);
+    case kOscF: return batch ? nullptr : factor9_kernel_f8(d, wide);
+    case kProductPeakF: return batch ? nullptr : factor9_kernel_f9(d, wide);
+    case kGaussianF: return batch ? nullptr : factor9_kernel_f10(d, wide);
+    case kC0F: return batch ? nullptr : factor9_kernel_f11(d, wide);
+    case kDiscontinuousF: return batch ? nullptr : factor9_kernel_f12(d, wide);
     default: return nullptr;
   }
 }
@@ -1139,6 +1192,8 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
   if (max_regions < n0) return GM_EINVAL;
   const int64_t cap = max_regions;
   const Layout lay = make_layout(d, cap);
+  // (the Gauss-Kronrod kernel has no factored form)
+  const int kfam = g_opt.rule == 1 ? fam : kernel_family(fam, d, params, lo, hi);
   g_last.valid = false;  // (before the workspace may move)
   char* base = fixed_base;
   int rc = GM_OK;
@@ -1271,7 +1326,7 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
       const int tg = tile_grid_for(nb);
       g_stats.lanes_per_region = lanes_of_mapping(map, d);
       if (timing) GM_HIP(hipEventRecord(ev[k][0], s));
-      GM_HIP(launch_rule(d, fam, map, ra, rg, s));
+      GM_HIP(launch_rule(d, kfam, map, ra, rg, s));
       if (timing) GM_HIP(hipEventRecord(ev[k][1], s));
       if (!g_opt.prune && !phases && nb <= kSmallStepRegions) {
         hipLaunchKernelGGL(small_step_fn(d), dim3(1), dim3(kTileThreads), 0, s, st, ra.partials,
@@ -1467,6 +1522,10 @@ int gm_eval_regions(int integrand_id, const double* params, int d, const double*
   GM_HIP(hipMemcpyAsync((void*)ra.H[0], hs.data(), sizeof(double) * d * n, hipMemcpyHostToDevice, s));
   GM_HIP(hipMemcpyAsync((void*)ra.L[0], ls.data(), sizeof(uint16_t) * n, hipMemcpyHostToDevice, s));
   const int map = choose_mapping(d, n);
+  // In chain form for every family: a region's err is a difference that a
+  // resolved region cancels down to rounding, and a list's values are returned
+  // one by one, so they keep the definition's order of operations (the launch is
+  // 5% of the call: 18 of 390 us for 30011 regions at d = 7).
   GM_HIP(launch_rule(d, integrand_id, map, ra, rule_grid(map, n, d), s));
   std::vector<uint8_t> ax((size_t)n);
   GM_HIP(hipMemcpyAsync(out_q, ra.Q, sizeof(double) * n, hipMemcpyDeviceToHost, s));

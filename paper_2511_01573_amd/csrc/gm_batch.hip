@@ -45,6 +45,7 @@ namespace gm {
 constexpr int kChunk = 1024;              // regions per chunk = threads per chunk workgroup
 constexpr int kChunkGrid = 2048;          // grid-stride workgroups of the chunk kernels
 constexpr int kMaxBatchItems = 65536;     // item slots the workspace is sized for
+constexpr int kMaxGroups = 78;            // (dimension, kernel family) pairs at most
 
 struct ItemState {
   int64_t off;     // segment start in the current buffer
@@ -575,8 +576,8 @@ struct BatchNode {
 }  // namespace
 
 size_t batch_layout_bytes(int dmax, int64_t cap) {
-  // per-item state for up to kMaxBatchItems items and 64 groups
-  return batch_layout(dmax, cap, kMaxBatchItems, 64).total;
+  // per-item state for up to kMaxBatchItems items and every group
+  return batch_layout(dmax, cap, kMaxBatchItems, kMaxGroups).total;
 }
 
 int set_tile(int d, int fam, int lanes, int grid) {
@@ -634,19 +635,27 @@ int run_batch(int n, const int* fam, const double* params, const int* d, const d
   }
   stats_reset();
   if (valid.empty()) return GM_OK;
-  // Group items by (d, family), stable.
+  // Kernel families: factored from d = 8 on under the degree-7 rule, where a
+  // batch's time is (kBatchFactorMinDim); a degree-9 batch is resolved by its
+  // initial partition at most dimensions and keeps the chain form throughout.
+  std::vector<int> kfam(fam, fam + n);
+  if (opt.rule == 0)
+    for (int i : valid)
+      if (d[i] >= kBatchFactorMinDim)
+        kfam[i] = kernel_family(fam[i], d[i], params + poff[i], lo + boff[i], hi + boff[i]);
+  // Group items by (d, kernel family), stable.
   std::stable_sort(valid.begin(), valid.end(), [&](int a, int b) {
-    return (d[a] != d[b]) ? d[a] < d[b] : fam[a] < fam[b];
+    return (d[a] != d[b]) ? d[a] < d[b] : kfam[a] < kfam[b];
   });
   const int nv = (int)valid.size();
   std::vector<int32_t> gfirst, glast, gd, gfam;
   for (int k = 0; k < nv; ++k) {
     const int i = valid[k];
-    if (k == 0 || d[i] != gd.back() || fam[i] != gfam.back()) {
+    if (k == 0 || d[i] != gd.back() || kfam[i] != gfam.back()) {
       gfirst.push_back(k);
       glast.push_back(k);
       gd.push_back(d[i]);
-      gfam.push_back(fam[i]);
+      gfam.push_back(kfam[i]);
     } else {
       glast.back() = k;
     }
@@ -786,7 +795,7 @@ int run_batch(int n, const int* fam, const double* params, const int* d, const d
       rfn[g] = opt.rule == 2 ? r9_kernel(gd[g], gfam[g], true) : gk_kernel(gd[g], gfam[g], true);
       rgrid[g] = 2048;
     } else {
-      const Tile t = tile_for(gd[g], gfam[g]);
+      const Tile t = tile_for(gd[g], base_family(gfam[g]));
       rfn[g] = rule_kernel(gd[g], gfam[g], t.log2l, true);
       rgrid[g] = t.grid > 0 ? t.grid : 2048;
     }

@@ -85,8 +85,24 @@ enum Family : int {
   kGaussian = 4,
   kC0 = 5,
   kDiscontinuous = 6,
-  kPolyF7 = 7
+  kPolyF7 = 7,
+  // Factored kernels of the families above (kernels only, gm_nodes.hpp; the
+  // host picks them, kernel_family).
+  kOscF = 8,
+  kProductPeakF = 9,
+  kGaussianF = 10,
+  kC0F = 11,
+  kDiscontinuousF = 12
 };
+// The integrand family a kernel family evaluates.
+constexpr int base_family(int kfam) {
+  return kfam == kOscF             ? kOsc
+         : kfam == kProductPeakF   ? kProductPeak
+         : kfam == kGaussianF      ? kGaussian
+         : kfam == kC0F            ? kC0
+         : kfam == kDiscontinuousF ? kDiscontinuous
+                                   : kfam;
+}
 
 // Integrand parameters as the kernels consume them.  a, u are the caller's;
 // inv_a2 = 1/(a*a) (product peak) and c0 = 2*pi*u_0 (oscillatory) are formed
@@ -300,7 +316,21 @@ RuleKernelFn rule_kernel_f4(int d, int log2l, bool batch);
 RuleKernelFn rule_kernel_f5(int d, int log2l, bool batch);
 RuleKernelFn rule_kernel_f6(int d, int log2l, bool batch);
 RuleKernelFn rule_kernel_f7(int d, int log2l, bool batch);
+// The same for the factored kernel families kOscF .. kDiscontinuousF (d >= kFactorMinDim).
+RuleKernelFn factor_kernel_f8(int d, int log2l, bool batch);
+RuleKernelFn factor_kernel_f9(int d, int log2l, bool batch);
+RuleKernelFn factor_kernel_f10(int d, int log2l, bool batch);
+RuleKernelFn factor_kernel_f11(int d, int log2l, bool batch);
+RuleKernelFn factor_kernel_f12(int d, int log2l, bool batch);
 constexpr int kTprMaxDim = 10;
+// Smallest dimension of the factored kernels, and of a batch's.  Below d = 7 a
+// region has at most 149 nodes and runs are bound by their launches (d = 3: 138
+// us with either kernel), and the initial partition often resolves an integral
+// to rounding, where err keeps its digits only under the definition's order of
+// operations; a batch, whose items' E are returned side by side, keeps that
+// order up to d = 7.
+constexpr int kFactorMinDim = 7;
+constexpr int kBatchFactorMinDim = 8;
 constexpr int kBatchMaxDim = kTprMaxDim;  // batch items have 2 <= d <= 10
 constexpr int kRuleBlockSize = 256;
 
@@ -330,6 +360,12 @@ RuleKernelFn rule9_kernel_f4(int d, bool batch, bool wide);
 RuleKernelFn rule9_kernel_f5(int d, bool batch, bool wide);
 RuleKernelFn rule9_kernel_f6(int d, bool batch, bool wide);
 RuleKernelFn rule9_kernel_f7(int d, bool batch, bool wide);
+// The same for the factored kernel families (single store only).
+RuleKernelFn factor9_kernel_f8(int d, bool wide);
+RuleKernelFn factor9_kernel_f9(int d, bool wide);
+RuleKernelFn factor9_kernel_f10(int d, bool wide);
+RuleKernelFn factor9_kernel_f11(int d, bool wide);
+RuleKernelFn factor9_kernel_f12(int d, bool wide);
 constexpr int rule9_log2l(int d) { return d - 5 < 2 ? 2 : (d - 5 > 6 ? 6 : d - 5); }
 // The wide mapping of the degree-9 kernel for active sets too small to fill
 // the GPU at rule9_log2l(d): up to 64 lanes per region (at least one corner

@@ -95,6 +95,53 @@ __device__ __forceinline__ void fourth_diff(const RuleConsts& K, double f0, doub
   sc = (fabs(fp2) + fabs(fm2) + 2.0 * fabs(f0)) + K.r7 * (fabs(fp3) + fabs(fm3) + 2.0 * fabs(f0));
 }
 
+// Class sums of the degree-7 rule into the rule value and error estimate.
+__device__ __forceinline__ void rule_combine(const RuleConsts& K, double s1, double s2, double s3,
+                                             double s4, double s5, double vol, RegionResult& r) {
+  r.nonfinite = !(isfinite(s1) && isfinite(s2) && isfinite(s3) && isfinite(s4) && isfinite(s5));
+  double q = K.w[0] * s1 + K.w[1] * s2;
+  q = q + K.w[2] * s3;
+  q = q + K.w[3] * s4;
+  q = q + K.w[4] * s5;
+  double er = K.e[0] * s1 + K.e[1] * s2;
+  er = er + K.e[2] * s3;
+  er = er + K.e[3] * s4;
+  er = er + K.e[4] * s5;
+  r.q = vol * q;
+  r.err = vol * fabs(er);
+}
+
+// Split axis (reading of Sec. 2): among the axes whose fourth difference is
+// within the noise band of the largest, the widest, then the first; and the
+// geometry guard, set when halving along it would change nothing.
+template <int D>
+__device__ __forceinline__ void split_axis(const RuleConsts& K, const double (&Dv)[D], double scale,
+                                           const double (&c)[D], const double (&h)[D],
+                                           RegionResult& r) {
+  double dmax = -1.0;
+#pragma unroll
+  for (int i = 0; i < D; ++i) dmax = Dv[i] > dmax ? Dv[i] : dmax;
+  const double thr = dmax - K.axis_band * scale;
+  int axis = -1;
+  double hb = 0.0, cb = 0.0;
+#pragma unroll
+  for (int i = 0; i < D; ++i) {
+    if (Dv[i] >= thr && (axis < 0 || h[i] > hb)) {
+      axis = i;
+      hb = h[i];
+      cb = c[i];
+    }
+  }
+  if (axis < 0) {
+    axis = 0;
+    hb = h[0];
+    cb = c[0];
+  }
+  const double hp = hb * 0.5;
+  r.axis = axis;
+  r.geo = (cb - hp == cb) || (cb + hp == cb) || (hp == 0.0);
+}
+
 // The (i, j) pair with lexicographic index p, i < j < D.
 template <int D>
 __device__ __forceinline__ void pair_of(int p, int& i, int& j) {

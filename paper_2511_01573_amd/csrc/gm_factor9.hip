@@ -1,0 +1,239 @@
+// gm_factor9.hip -- the degree-9 rule kernel for the factored families: the
+// rule, embedded rules, error models and split axis of gm_rule9.hip (the
+// "9-order" reading of arXiv 2511.01573, Sec. 2) with the node values of
+// gm_nodes.hpp.
+//
+// Mapping: L lanes of one wavefront per region as in gm_rule9.hip.  The
+// region's factors, and the products of its centre factors before an axis,
+// after it and strictly between two, are formed by its lanes together in LDS,
+// so a node of an axis pair or triple (77% of the 1089 nodes at d = 8) is two
+// to four multiplications of shared products instead of an exponential behind a
+// chain over the axes that it does not move.
+#include "gm_nodes.hpp"
+#include "gm_rule9.hpp"
+
+namespace gm {
+
+template <int D, int FAM>
+struct Factor9Slot {
+  using T = typename Alg<FAM>::T;
+  static constexpr bool U = Alg<FAM>::kUnitCentre;
+  // per-coordinate terms at the perturbed positions: [0] +l2, [1] -l2,
+  // [2] +l3 (= +l4), [3] -l3, [4] +l6, [5] -l6; after the axis nodes, which
+  // alone use l6, [4] and [5] hold +l5 and -l5
+  T tp[6][D];
+  T tc[U ? 1 : D], pre[U ? 1 : D], suf[U ? 1 : D];
+  T mid[U ? 1 : D * (D - 1) / 2];  // strictly between axes i < j: [j (j - 1) / 2 + i]
+  double dv[D], sc[D];
+};
+
+// Three wavefronts per SIMD up to d = 10 (at most a few values spill to
+// scratch, and the extra wavefront hides more latency); two above, where the
+// spill would grow.
+template <int D, int FAM, int LOG2L>
+__global__ __launch_bounds__(kRuleBlock) __attribute__((amdgpu_waves_per_eu(D <= 10 ? 3 : 2)))
+void factor9_kernel(RuleArgs A) {
+  using F = Alg<FAM>;
+  using T = typename F::T;
+  constexpr bool U = F::kUnitCentre;
+  constexpr int L = 1 << LOG2L;
+  constexpr int RPB = kRuleBlock / L;  // regions per block step
+  constexpr int NPAIR = D * (D - 1) / 2;
+  constexpr int NTRI = D * (D - 1) * (D - 2) / 6;
+  static_assert(LOG2L <= D && LOG2L <= 6, "at least one corner and one wavefront per region");
+  __shared__ Factor9Slot<D, FAM> slots[RPB];
+  int64_t start, n;
+  int buf;
+  if (!active_range<false>(A, start, n, buf)) return;
+  const RegionSrc R = region_src<false>(A, buf);
+  const RuleConsts& K = A.K;
+  const int g = threadIdx.x >> LOG2L;  // region slot in the block
+  const int s = threadIdx.x & (L - 1);
+  Factor9Slot<D, FAM>& sl = slots[g];
+  dd qs = {0.0, 0.0}, es = {0.0, 0.0};
+  int nonfin = 0;
+  for (int64_t rb = start + (int64_t)blockIdx.x * RPB; rb < n; rb += (int64_t)gridDim.x * RPB) {
+    const int64_t r = rb + g;
+    const bool valid = r < n;
+    double volo;
+    const DevParams& P = region_params<false>(A, buf, valid ? r : start, volo);
+    double c[D], h[D];
+    int lvl = 0;
+    if (valid) {
+      lvl = load_region<D>(R, r, c, h);
+    } else {
+#pragma unroll
+      for (int j = 0; j < D; ++j) {
+        c[j] = 0.5;
+        h[j] = 0.25;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < D; ++j) {
+      if ((j & (L - 1)) == s) {
+        F::pair(P, j, c[j], h[j], K.lam2, sl.tp[0][j], sl.tp[1][j]);
+        F::pair(P, j, c[j], h[j], K.lam3, sl.tp[2][j], sl.tp[3][j]);
+        F::pair(P, j, c[j], h[j], K.lam6, sl.tp[4][j], sl.tp[5][j]);
+        if constexpr (!U) {
+          const double x[1] = {c[j]};
+          T t[1];
+          F::template terms<1>(P, j, x, t);
+          sl.tc[j] = t[0];
+        }
+      }
+    }
+    const T base = F::template base<D>(P, c);
+    __syncthreads();
+    T full = base;
+    if constexpr (!U) {
+      // by rows (first axis i)
+      for (int i = s; i < D; i += L) {
+        T m = F::none();
+        for (int j = i + 1; j < D; ++j) {
+          sl.mid[j * (j - 1) / 2 + i] = m;
+          m = F::comb(m, sl.tc[j]);
+        }
+        sl.suf[i] = m;
+        m = F::none();
+        for (int j = 0; j < i; ++j) m = F::comb(m, sl.tc[j]);
+        sl.pre[i] = m;
+      }
+      __syncthreads();
+      full = F::comb(sl.pre[D - 1], sl.tc[D - 1]);
+    }
+    const double f0 = F::value(full);
+    KSum S2 = {0.0, 0.0}, S3 = {0.0, 0.0}, S4 = {0.0, 0.0}, S5 = {0.0, 0.0};
+    KSum S6 = {0.0, 0.0}, S7 = {0.0, 0.0}, S8 = {0.0, 0.0};
+    // The three node groups run one after the other, so the lanes of a
+    // wavefront stay on the same code path.
+    // Axes: +-l2, +-l3, +-l6 along axis i and its fourth difference.
+    for (int i = s; i < D; i += L) {
+      const T b[6] = {sl.tp[0][i], sl.tp[1][i], sl.tp[2][i], sl.tp[3][i], sl.tp[4][i], sl.tp[5][i]};
+      double f[6];
+      T o = base;
+      if constexpr (!U) o = F::comb(sl.pre[i], sl.suf[i]);
+      const T a[6] = {o, o, o, o, o, o};
+      F::template nodes<6>(a, b, f);
+      ks_add(S2, f[0] + f[1]);
+      ks_add(S3, f[2] + f[3]);
+      ks_add(S6, f[4] + f[5]);
+      double dv, scv;
+      fourth_diff(K, f0, f[0], f[1], f[2], f[3], dv, scv);
+      sl.dv[i] = dv;
+      sl.sc[i] = scv;
+    }
+    // the corner terms take the l6 terms' place (each lane the axes it alone
+    // read there)
+#pragma unroll
+    for (int j = 0; j < D; ++j) {
+      if ((j & (L - 1)) == s) F::pair(P, j, c[j], h[j], K.lam5, sl.tp[4][j], sl.tp[5][j]);
+    }
+    // Axis pairs i < j: class 4 (+-l4, +-l4) and class 7 in both orders.
+    for (int it = s; it < NPAIR; it += L) {
+      const int pk = kItems<D>.pair[it];
+      const int i = pk & 15, j = pk >> 4;
+      T o = base;
+      if constexpr (!U) o = F::comb(F::comb(sl.pre[i], sl.mid[it]), sl.suf[j]);
+      const T i3p = F::comb(o, sl.tp[2][i]), i3m = F::comb(o, sl.tp[3][i]);
+      const T i2p = F::comb(o, sl.tp[0][i]), i2m = F::comb(o, sl.tp[1][i]);
+      const T j3p = sl.tp[2][j], j3m = sl.tp[3][j], j2p = sl.tp[0][j], j2m = sl.tp[1][j];
+      // class 4, then class 7: (+-l3 on i, +-l2 on j) and (+-l2 on i, +-l3 on j)
+      const T a[12] = {i3p, i3p, i3m, i3m, i3p, i3p, i3m, i3m, i2p, i2p, i2m, i2m};
+      const T b[12] = {j3p, j3m, j3p, j3m, j2p, j2m, j2p, j2m, j3p, j3m, j3p, j3m};
+      double f[12];
+      F::template nodes<12>(a, b, f);
+      ks_add(S4, (f[0] + f[1]) + (f[2] + f[3]));
+      ks_add(S7, ((f[4] + f[5]) + (f[6] + f[7])) + ((f[8] + f[9]) + (f[10] + f[11])));
+    }
+    // Axis triples i < j < k: class 8.
+    for (int it = s; it < NTRI; it += L) {
+      const int tk3 = kItems<D>.tri[it];
+      const int i = tk3 & 15, j = (tk3 >> 4) & 15, k = tk3 >> 8;
+      T o = base;
+      if constexpr (!U)
+        o = F::comb(F::comb(sl.pre[i], sl.mid[j * (j - 1) / 2 + i]),
+                    F::comb(sl.mid[k * (k - 1) / 2 + j], sl.suf[k]));
+      const T ip = F::comb(o, sl.tp[2][i]), im = F::comb(o, sl.tp[3][i]);
+      const T jp = sl.tp[2][j], jm = sl.tp[3][j], kp = sl.tp[2][k], km = sl.tp[3][k];
+      const T pp = F::comb(ip, jp), pm = F::comb(ip, jm), mp = F::comb(im, jp), mm = F::comb(im, jm);
+      const T a[8] = {pp, pp, pm, pm, mp, mp, mm, mm}, b[8] = {kp, km, kp, km, kp, km, kp, km};
+      double f[8];
+      F::template nodes<8>(a, b, f);
+      ks_add(S8, ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7])));
+    }
+    __syncthreads();
+    // Class 5: this lane's 2^(D - LOG2L) corners.
+    {
+      T t5p[D], t5m[D];
+#pragma unroll
+      for (int j = 0; j < D; ++j) {
+        t5p[j] = sl.tp[4][j];
+        t5m[j] = sl.tp[5][j];
+      }
+      corner_sum<D, FAM, LOG2L>(base, t5p, t5m, (uint32_t)s, S5);
+    }
+    // Combine the L lanes of the region: each lane's compensated class sums
+    // are rounded once and added across the lanes in a butterfly (a + b and
+    // b + a round alike, so every lane ends with the same totals).
+    double Ts[7] = {ks_val(S2), ks_val(S3), ks_val(S4), ks_val(S5),
+                   ks_val(S6), ks_val(S7), ks_val(S8)};
+#pragma unroll
+    for (int m = L / 2; m >= 1; m >>= 1) {
+#pragma unroll
+      for (int q = 0; q < 7; ++q) Ts[q] = Ts[q] + __shfl_xor(Ts[q], m, 64);
+    }
+    __syncthreads();
+    if (s == 0 && valid) {
+      const double vol = ldexp(volo, -lvl);
+      RegionResult o;
+      rule9_combine(K, f0, Ts, vol, o);
+      double dv[D], scale = 0.0;
+#pragma unroll
+      for (int i = 0; i < D; ++i) {
+        dv[i] = sl.dv[i];
+        scale = sl.sc[i] > scale ? sl.sc[i] : scale;
+      }
+      split_axis<D>(K, dv, scale, c, h, o);
+      o.nonfinite |= !Fam<base_family(FAM)>::in_range(P, c, h);
+      store_result(A, r, o);
+      dd_add(qs, o.q);
+      dd_add(es, o.err);
+      nonfin |= o.nonfinite;
+    }
+    __syncthreads();
+  }
+  block_partials(A, qs, es, nonfin);
+}
+
+#ifndef GM_RULE_FAMILY
+#error "compile with -DGM_RULE_FAMILY=<8..12>"
+#endif
+
+#define GM_F9_CAT2(a, b) a##b
+#define GM_F9_CAT(a, b) GM_F9_CAT2(a, b)
+
+template <int D>
+static RuleKernelFn f9_pick(bool wide) {
+  if (wide) return factor9_kernel<D, GM_RULE_FAMILY, rule9_log2l_wide(D)>;
+  return factor9_kernel<D, GM_RULE_FAMILY, rule9_log2l(D)>;
+}
+
+RuleKernelFn GM_F9_CAT(factor9_kernel_f, GM_RULE_FAMILY)(int d, bool wide) {
+  switch (d) {
+    case 7: return f9_pick<7>(wide);
+    case 8: return f9_pick<8>(wide);
+    case 9: return f9_pick<9>(wide);
+    case 10: return f9_pick<10>(wide);
+    case 11: return f9_pick<11>(wide);
+    case 12: return f9_pick<12>(wide);
+    case 13: return f9_pick<13>(wide);
+    case 14: return f9_pick<14>(wide);
+    case 15: return f9_pick<15>(wide);
+    case 16: return f9_pick<16>(wide);
+    default: return nullptr;
+  }
+}
+
+GM_CHECK_UNIT_F(factor9, GM_RULE_FAMILY)
+
+}  // namespace gm

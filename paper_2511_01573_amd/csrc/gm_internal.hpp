@@ -57,6 +57,9 @@ void fill_consts(int d, RuleConsts& K);
 void fill_params(int fam, int d, const double* params, DevParams& P);
 int validate(int fam, const double* params, int d, const double* lo, const double* hi,
              double rel_tol, double abs_tol);
+// The kernel family (gm_common.hpp Family) that evaluates integrand fam with
+// these parameters on [lo, hi] in an adaptive run.
+int kernel_family(int fam, int d, const double* params, const double* lo, const double* hi);
 hipError_t launch_rule(int d, int fam, int log2l, const RuleArgs& a, int grid, hipStream_t s);
 // Rule-kernel mapping for n regions of dimension d: -1 = one lane per region,
 // else log2 of the lanes per region.
@@ -104,6 +107,13 @@ GM_DECLARE_POLL_F(rule9)
 GM_DECLARE_POLL_F(adjoint)
 GM_DECLARE_POLL_F(gk)
 #undef GM_DECLARE_POLL_F
+#define GM_DECLARE_POLL_FACTOR(name)                                                     \
+  int gm_check_poll_##name##_f8(CheckRec*); int gm_check_poll_##name##_f9(CheckRec*);    \
+  int gm_check_poll_##name##_f10(CheckRec*); int gm_check_poll_##name##_f11(CheckRec*);  \
+  int gm_check_poll_##name##_f12(CheckRec*);
+GM_DECLARE_POLL_FACTOR(factor)
+GM_DECLARE_POLL_FACTOR(factor9)
+#undef GM_DECLARE_POLL_FACTOR
 #endif
 
 // The retired-leaf store of the last gradient-mode forward run (SoA).

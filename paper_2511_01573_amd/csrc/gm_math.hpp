@@ -199,6 +199,72 @@ GM_HD void sin_n(const double (&x)[N], double (&y)[N]) {
   }
 }
 
+// sin and cos of x + xl (xl a correction far below x) with the reduction and
+// polynomials of cos_n and sin_n: x = r + k pi, r = rh + rl.  One reduction
+// serves both.  REDUCED_TAIL = false leaves rl out (for angles that carry a
+// rounding of their own of that size).
+template <int N, bool REDUCED_TAIL>
+GM_HD void sincos_n(const double (&x)[N], const double (&xl)[N], double (&sn)[N], double (&cs)[N]) {
+  double t[N], kd[N], r1[N], rh[N], rl[N], z[N], q[N], p[N], hi[N], lo[N];
+  int32_t k[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    t[i] = fma(x[i], kInvPi, kShift);
+    kd[i] = t[i] - kShift;
+    k[i] = low_word(t[i]);
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) r1[i] = fma(-kd[i], kPi_1, x[i]);
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    rh[i] = fma(-kd[i], kPi_2, r1[i]);
+    rl[i] = REDUCED_TAIL ? fma(-kd[i], kPi_3, fma(-kd[i], kPi_2, r1[i] - rh[i])) + xl[i] : 0.0;
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    z[i] = rh[i] * rh[i];
+    q[i] = kCosPoly[0];
+    p[i] = kSinPoly[0];
+  }
+#pragma unroll
+  for (int cc = 1; cc < 8; ++cc) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) q[i] = fma(q[i], z[i], kCosPoly[cc]);
+#pragma unroll
+    for (int i = 0; i < N; ++i) p[i] = fma(p[i], z[i], kSinPoly[cc]);
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    p[i] = fma(p[i], z[i], kSinPoly[8]);
+    hi[i] = fma(z[i], -0.5, 1.0);
+    lo[i] = fma(z[i], -0.5, 1.0 - hi[i]);
+    if (REDUCED_TAIL) {
+      lo[i] = fma(-rh[i], rl[i], lo[i]);
+      sn[i] = rh[i] + fma(rh[i] * z[i], p[i], rl[i] * hi[i]);
+    } else {
+      sn[i] = fma(rh[i] * z[i], p[i], rh[i]);
+    }
+    cs[i] = hi[i] + fma(z[i] * z[i], q[i], lo[i]);
+  }
+  // both change sign with each half turn: bit 0 of k moved into the sign bits
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const uint32_t sg = (uint32_t)k[i] << 31;
+#if defined(__HIP_DEVICE_COMPILE__)
+    sn[i] = __hiloint2double(__double2hiint(sn[i]) ^ (int)sg, __double2loint(sn[i]));
+    cs[i] = __hiloint2double(__double2hiint(cs[i]) ^ (int)sg, __double2loint(cs[i]));
+#else
+    uint32_t w[2];
+    std::memcpy(w, &sn[i], sizeof w);
+    w[1] ^= sg;
+    std::memcpy(&sn[i], w, sizeof w);
+    std::memcpy(w, &cs[i], sizeof w);
+    w[1] ^= sg;
+    std::memcpy(&cs[i], w, sizeof w);
+#endif
+  }
+}
+
 // 1/x: the hardware reciprocal estimate refined by two Newton steps
 // e = 1 - x r, r += r e (each step squares the relative error), within 1 ulp
 // for |x| in [2^-1022, 2^1022].  Outside that range (reciprocals beyond the

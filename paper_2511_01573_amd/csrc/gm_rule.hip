@@ -41,21 +41,6 @@ namespace gm {
 #define GM_UNROLL_A4 64
 #endif
 
-__device__ __forceinline__ void rule_combine(const RuleConsts& K, double s1, double s2, double s3,
-                                             double s4, double s5, double vol, RegionResult& r) {
-  r.nonfinite = !(isfinite(s1) && isfinite(s2) && isfinite(s3) && isfinite(s4) && isfinite(s5));
-  double q = K.w[0] * s1 + K.w[1] * s2;
-  q = q + K.w[2] * s3;
-  q = q + K.w[3] * s4;
-  q = q + K.w[4] * s5;
-  double er = K.e[0] * s1 + K.e[1] * s2;
-  er = er + K.e[2] * s3;
-  er = er + K.e[3] * s4;
-  er = er + K.e[4] * s5;
-  r.q = vol * q;
-  r.err = vol * fabs(er);
-}
-
 // ---------------------------------------------------------------------------
 // TPR: one lane per region (d <= 10).
 // ---------------------------------------------------------------------------
@@ -144,28 +129,7 @@ __device__ __forceinline__ RegionResult rule_region_tpr(const DevParams& P, cons
 
   RegionResult r;
   rule_combine(K, f0, ks_val(S2), ks_val(S3), ks_val(S4), ks_val(S5), vol, r);
-  double dmax = -1.0;
-#pragma unroll
-  for (int i = 0; i < D; ++i) dmax = Dv[i] > dmax ? Dv[i] : dmax;
-  const double thr = dmax - K.axis_band * scale;
-  int axis = -1;
-  double hb = 0.0, cb = 0.0;
-#pragma unroll
-  for (int i = 0; i < D; ++i) {
-    if (Dv[i] >= thr && (axis < 0 || h[i] > hb)) {
-      axis = i;
-      hb = h[i];
-      cb = c[i];
-    }
-  }
-  if (axis < 0) {
-    axis = 0;
-    hb = h[0];
-    cb = c[0];
-  }
-  const double hp = hb * 0.5;
-  r.axis = axis;
-  r.geo = (cb - hp == cb) || (cb + hp == cb) || (hp == 0.0);
+  split_axis<D>(K, Dv, scale, c, h, r);
   r.nonfinite |= !F::in_range(P, c, h);
   return r;
 }

@@ -29,7 +29,7 @@
 // sum enters the class's compensated total.  Every node argument is the
 // left-to-right chain of the per-coordinate terms, as in the degree-7 kernel,
 // so node values match the defining formula's evaluation order bitwise.
-#include "gm_corner.hpp"
+#include "gm_rule9.hpp"
 
 namespace gm {
 
@@ -40,31 +40,6 @@ struct R9Slot {
   // [2] +l3 (= +l4), [3] -l3, [4] +l6, [5] -l6
   double tp[6][D];
 };
-
-// Work-item tables: the axis pairs (i, j) and triples (i, j, k), packed 4
-// bits per index, ordered by their last index so that the lanes of a round
-// run tail chains of about the same length.
-template <int D>
-struct ItemTable {
-  uint16_t pair[D * (D - 1) / 2 + 1];
-  uint16_t tri[D * (D - 1) * (D - 2) / 6 + 1];
-};
-
-template <int D>
-constexpr ItemTable<D> make_items() {
-  ItemTable<D> t{};
-  int n = 0;
-  for (int j = 1; j < D; ++j)
-    for (int i = 0; i < j; ++i) t.pair[n++] = (uint16_t)(i | (j << 4));
-  n = 0;
-  for (int k = 2; k < D; ++k)
-    for (int j = 1; j < k; ++j)
-      for (int i = 0; i < j; ++i) t.tri[n++] = (uint16_t)(i | (j << 4) | (k << 8));
-  return t;
-}
-
-template <int D>
-__device__ constexpr ItemTable<D> kItems = make_items<D>();
 
 // Extend N node arguments by the centre terms of coordinates k0 .. k1-1, in
 // order (one loop for all N chains: each step is one LDS read and N (+)).
@@ -246,32 +221,8 @@ void rule9_kernel(RuleArgs A) {
     __syncthreads();
     if (s == 0 && valid) {
       const double vol = ldexp(volo, -lvl);
-      const double S[8] = {f0, T[0], T[1], T[2], T[3], T[4], T[5], T[6]};
       RegionResult o;
-      o.nonfinite = 0;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) o.nonfinite |= !isfinite(S[q]);
-      double q9 = K.w9[0] * S[0];
-      double n1 = K.e9[0] * S[0];
-#pragma unroll
-      for (int q = 1; q < 8; ++q) {
-        q9 = q9 + K.w9[q] * S[q];
-        n1 = n1 + K.e9[q] * S[q];
-      }
-      n1 = fabs(n1);
-      double q7 = K.w[0] * S[0];
-      double d75 = K.e[0] * S[0];
-#pragma unroll
-      for (int q = 1; q < 5; ++q) {
-        q7 = q7 + K.w[q] * S[q];
-        d75 = d75 + K.e[q] * S[q];
-      }
-      const double n2 = fabs(d75);
-      const double q5 = q7 - d75;
-      const double q3 = K.q3[0] * S[0] + K.q3[1] * S[2];
-      const double n3 = fabs(q5 - q3);
-      o.q = vol * q9;
-      o.err = K.err_model ? vol * (n1 * fmin(1.0, 2.0 * fmax(n1 / n2, n2 / n3))) : vol * n1;
+      rule9_combine(K, f0, T, vol, o);
       double dmax = -1.0, scale = 0.0;
       for (int i = 0; i < D; ++i) {
         dmax = sl.dv[i] > dmax ? sl.dv[i] : dmax;

@@ -1,0 +1,115 @@
+"""The factored rule kernels (csrc/gm_nodes.hpp: per-axis factors formed once per
+region), which adaptive runs of dimension >= 7 use: every mapping at the edges
+of its range, both fully symmetric rules, every family, against the chain-form
+kernels (gm_eval_regions) on every region of the last active set and against the
+oracle on a sample; and parameters on either side of the line beyond which a run
+keeps the chain form (the axes' largest |log factor| adding up to 500).
+
+Tolerance: the per-region bar of parity.py, 1e-13 of the magnitudes summed.  The
+factored value of a node differs from the chain's by the rounding of d factors
+and d products, and the chain's own by that of an exponent or angle s, |s| 2^-53
+a few times: below 3e-14 for every case here (|s| <= 60)."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_2511_01573_amd import gm, workloads as W
+from parity import assert_regions_match
+
+pytestmark = pytest.mark.gpu
+
+FACTORED = [1, 2, 4, 5, 6]  # families with a factored kernel
+MAPPINGS = {7: (1, 4), 8: (1, 4, 16), 10: (1, 16, 64), 11: (4, 64), 13: (4, 16), 16: (16, 64)}
+
+
+def _stopped_run(fam, p, lo, hi, iters, rule=0, lanes=0, init_log2=9):
+    opts = {"max_iters": iters, "rule": rule, "lanes_per_region": lanes,
+            "init_log2_regions": init_log2}
+    for k, v in opts.items():
+        gm.set_option(k, v)
+    try:
+        _, _, st = gm.integrate(fam, p, lo, hi, 1e-12, 1e-300, 1 << 16)
+        assert st in (gm.MAX_ITERS, gm.MAX_REGIONS, gm.OK)
+        act = gm.last_active(len(lo))
+    finally:
+        for k, v in {"max_iters": 10000, "lanes_per_region": 0, "init_log2_regions": 12}.items():
+            gm.set_option(k, v)
+    try:
+        chain = gm.eval_regions(fam, p, lo, hi, act["c"], act["h"], act["lvl"])
+    finally:
+        gm.set_option("rule", 0)
+    return act, chain
+
+
+def _check(fam, p, lo, hi, act, chain, rule, label):
+    n = act["lvl"].size
+    assert n > 0
+    vol = 1.0
+    for a, b in zip(lo, hi):
+        vol = vol * (b - a)
+    idx = np.unique(np.linspace(0, n - 1, min(n, 24)).astype(int))
+    ref = O.rule_many(fam, p, act["c"][idx], act["h"][idx], act["lvl"][idx], vol, rule_id=rule)
+    assert_regions_match(act["Q"][idx], act["err"][idx], act["axis"][idx], ref, label)
+    q, err, axis = chain
+    # every region against the chain form; the scale of the sample's largest
+    # (err cancels magnitudes of the size of scaleE, a multiple of scaleQ)
+    ratio = np.max(ref["scaleE"] / np.maximum(ref["scaleQ"], 1e-300))
+    scale = np.max(ref["scaleQ"] * np.ldexp(1.0, act["lvl"][idx])) * np.ldexp(1.0, -act["lvl"])
+    assert np.all(np.abs(act["Q"] - q) <= 1e-13 * scale), label
+    assert np.all(np.abs(act["err"] - err) <= 1e-13 * scale * max(ratio, 1.0)), label
+    assert np.array_equal(act["axis"], axis), label
+
+
+@pytest.mark.parametrize("d", sorted(MAPPINGS))
+@pytest.mark.parametrize("fam", FACTORED)
+def test_degree7_mappings(fam, d):
+    p = W.family_params(fam, d, seed=700 * fam + d)
+    lo, hi = W.unit_box(d)
+    for lanes in MAPPINGS[d]:
+        print(f"case fam={fam} d={d} lanes={lanes}", flush=True)
+        act, chain = _stopped_run(fam, p, lo, hi, 4 if d <= 11 else 3, lanes=lanes)
+        _check(fam, p, lo, hi, act, chain, 0, f"fam{fam} d{d} lanes{lanes}")
+
+
+@pytest.mark.parametrize("d,iters,init_log2", [(7, 3, 7), (8, 2, 12), (9, 9, 3), (12, 2, 6),
+                                               (16, 2, 6)])
+@pytest.mark.parametrize("fam", FACTORED)
+def test_degree9_mappings(fam, d, iters, init_log2):
+    p = W.family_params(fam, d, seed=900 * fam + d)
+    lo, hi = W.unit_box(d)
+    print(f"case degree 9 fam={fam} d={d}", flush=True)
+    act, chain = _stopped_run(fam, p, lo, hi, iters, rule=2, init_log2=init_log2)
+    _check(fam, p, lo, hi, act, chain, 2, f"degree 9 fam{fam} d{d}")
+
+
+@pytest.mark.parametrize("fam,a,u,box", [
+    (2, 50.0, 0.5, (0.0, 1.0)),        # the paper's f2
+    (2, 2e13, 2.0, (0.0, 1.0)),        # factors 1 / (x - 2)^2: log factors 61 + 1.4 per axis
+    (2, 6e15, 2.0, (0.0, 1.0)),        # beyond the line
+    (4, 7.9, 1.0, (0.0, 1.0)),         # span 499
+    (4, 8.0, 1.0, (0.0, 1.0)),         # 512
+    (5, -62.0, 0.0, (0.0, 1.0)),       # growing factors, span 496
+    (5, -63.0, 0.0, (0.0, 1.0)),       # 504
+    (6, -3.0, 9.0, (0.0, 10.0)),       # a cut outside most of the box
+    (1, 3.0, 0.25, (-2.0, 3.0)),
+])
+def test_both_sides_of_the_line(fam, a, u, box):
+    d = 8
+    lo, hi = np.full(d, box[0]), np.full(d, box[1])
+    # alternate the sign of the exponents where the family allows it
+    av = np.full(d, a)
+    if fam in (1, 5):
+        av[1::2] *= -0.5
+    p = np.concatenate([av, np.full(d, u)])
+    print(f"case line fam={fam} a={a}", flush=True)
+    act, _ = _stopped_run(fam, p, lo, hi, 2)
+    vol = (box[1] - box[0]) ** d
+    idx = np.unique(np.linspace(0, act["lvl"].size - 1, 40).astype(int))
+    ref = O.rule_many(fam, p, act["c"][idx], act["h"][idx], act["lvl"][idx], vol)
+    # beyond e^-60 the oracle's own sum of exponents rounds by up to 500 2^-53
+    # times the d additions, 4.4e-13
+    tol = 4.4e-13 if fam in (4, 5) else 1e-13
+    assert np.all(np.abs(act["Q"][idx] - ref["Q"]) <= tol * np.maximum(np.abs(ref["Q"]), ref["scaleQ"]))
+    assert np.all(np.abs(act["err"][idx] - ref["err"]) <= tol * ref["scaleE"])
