@@ -964,7 +964,8 @@ RuleKernelFn gk_kernel(int d, int fam, bool batch) {
   }
 }
 
-RuleKernelFn r9_kernel(int d, int fam, bool batch, bool wide) {
+RuleKernelFn r9_kernel(int d, int fam, bool batch, int log2l) {
+  const bool wide = log2l != rule9_log2l(d);
   switch (fam) {
     case 1: return rule9_kernel_f1(d, batch, wide);
     case 2: return rule9_kernel_f2(d, batch, wide);
@@ -973,22 +974,23 @@ RuleKernelFn r9_kernel(int d, int fam, bool batch, bool wide) {
     case 5: return rule9_kernel_f5(d, batch, wide);
     case 6: return rule9_kernel_f6(d, batch, wide);
     case 7: return rule9_kernel_f7(d, batch, wide);
-    case kOscF: return batch ? nullptr : factor9_kernel_f8(d, wide);
-    case kProductPeakF: return batch ? nullptr : factor9_kernel_f9(d, wide);
-    case kGaussianF: return batch ? nullptr : factor9_kernel_f10(d, wide);
-    case kC0F: return batch ? nullptr : factor9_kernel_f11(d, wide);
-    case kDiscontinuousF: return batch ? nullptr : factor9_kernel_f12(d, wide);
+    case kOscF: return batch ? nullptr : factor9_kernel_f8(d, log2l);
+    case kProductPeakF: return batch ? nullptr : factor9_kernel_f9(d, log2l);
+    case kGaussianF: return batch ? nullptr : factor9_kernel_f10(d, log2l);
+    case kC0F: return batch ? nullptr : factor9_kernel_f11(d, log2l);
+    case kDiscontinuousF: return batch ? nullptr : factor9_kernel_f12(d, log2l);
     default: return nullptr;
   }
 }
 
 // Mapping codes: the Gauss-Kronrod kernel (gk_threads(d) per region), and the
-// degree-9 kernel with 2^(code - kMapR9) lanes per region.
+// degree-9 kernel with 2^(code - kMapR9) lanes per region (kMapR9Tpr: one lane).
 constexpr int kMapGk = 100;
 constexpr int kMapR9 = 200;
+constexpr int kMapR9Tpr = kMapR9 - 1;
 
 int lanes_of_mapping(int map, int d) {
-  return map == kMapGk ? gk_threads(d) : map >= kMapR9 ? (1 << (map - kMapR9)) : map < 0 ? 1 : (1 << map);
+  return map == kMapGk ? gk_threads(d) : map >= kMapR9 ? (1 << (map - kMapR9)) : map < 0 || map == kMapR9Tpr ? 1 : (1 << map);
 }
 
 int64_t nodes_per_region(int d) {
@@ -1006,7 +1008,7 @@ int64_t nodes_per_region(int d) {
 
 hipError_t launch_rule(int d, int fam, int log2l, const RuleArgs& a, int grid, hipStream_t s) {
   RuleKernelFn fn = log2l == kMapGk    ? gk_kernel(d, fam, false)
-                    : log2l >= kMapR9 ? r9_kernel(d, fam, false, log2l - kMapR9 != rule9_log2l(d))
+                    : log2l >= kMapR9Tpr ? r9_kernel(d, fam, false, log2l - kMapR9)
                                       : rule_kernel(d, fam, log2l, false);
   if (!fn) return hipErrorInvalidValue;
   hipLaunchKernelGGL(fn, dim3(grid), dim3(kRuleBlockSize), 0, s, a);
@@ -1021,33 +1023,62 @@ bool mapping_allowed(int d, int log2l) {
   return false;
 }
 
-// Lanes the rule kernel should occupy: 256 CUs x 4 SIMDs x 2 wavefronts x 64.
-constexpr int64_t kTargetLanes = 131072;
+// log2 of the lanes per region the option asks for (-1: one lane).
+static int forced_log2l() {
+  int l = -1;
+  if (g_opt.lanes_per_region > 1) {
+    l = 0;
+    while ((1 << l) < g_opt.lanes_per_region) ++l;
+  }
+  return l;
+}
 
-int choose_mapping(int d, int64_t n) {
+// Lanes a launch should occupy before it takes fewer lanes per region: the
+// whole GPU at two wavefronts per SIMD is 256 CUs x 4 SIMDs x 2 x 64 = 131072,
+// but a lane's whole region costs less than several lanes' shares with their
+// common work, so the one-lane kernel wins from fewer on.  Rule kernel at d = 8,
+// corner peak, us for 1 / 4 / 16 lanes: n = 8192: 22 / 19 / 19, 32768: 24 / 30 /
+// 40, 65536: 24 / 43 / 75; d = 10: n = 32768: 59 / 46 / 62, 65536: 69 / 82 / 112.
+// Factored, d = 13 product peak, 1 / 4 / 16 / 64 lanes: n = 1024: 38 / 29 / 30 /
+// 24, 4096: 42 / 28 / 23 / 37, 16384: 43 / 29 / 38 / 91, 65536: 46 / 77 / 132 /
+// 345; up to d = 10 one lane is the fastest at every n (d = 8 Gaussian, n = 256:
+// 11 / 15 / 19 us, 49166: 18 / 30 / 65).
+constexpr int64_t kTargetLanes = 131072;
+static int64_t target_lanes(int d, bool factored) {
+  if (factored) return d <= kTprMaxDim ? 0 : 65536;
+  return d < 10 ? 32768 : d == 10 ? 65536 : kTargetLanes;
+}
+// Active sets from which the factored degree-9 rule runs one lane per region: at
+// every size up to d = 9 (d = 8 Gaussian, one lane against the several it
+// replaces, n = 256: 16 / 21 us, 4096: 17 / 33, 65536: 20 / 73); at d = 10 the
+// 64-lane kernel is ahead in small sets (n = 1024: 30 / 21, 4096: 32 / 35).
+constexpr int64_t r9_tpr_regions(int d) { return d < 10 ? 0 : 4096; }
+
+int choose_mapping(int d, int kfam, int64_t n, bool list) {
+  const bool factored = base_family(kfam) != kfam;
   if (g_opt.rule == 1) return kMapGk;
   if (g_opt.rule == 2) {
+    if (factored && d <= kTprMaxDim && n >= r9_tpr_regions(d)) return kMapR9Tpr;
     // the wide mapping while the default one would leave the GPU mostly idle
     const bool wide = (n << rule9_log2l(d)) < kTargetLanes;
     return kMapR9 + (wide ? rule9_log2l_wide(d) : rule9_log2l(d));
   }
-  const int forced = g_opt.lanes_per_region;
-  if (forced > 0) {
-    int l = -1;
-    if (forced > 1) {
-      l = 0;
-      while ((1 << l) < forced) ++l;
-    }
-    if (mapping_allowed(d, l)) return l;
+  const bool tpr = d <= kTprMaxDim || factored;
+  if (g_opt.lanes_per_region > 0) {
+    const int l = forced_log2l();
+    if (l < 0 ? tpr : mapping_allowed(d, l)) return l;
   }
+  // (a list's mapping, and with it the order in which its class sums are
+  // combined, stays that of the full GPU)
+  const int64_t target = list ? kTargetLanes : target_lanes(d, factored);
   const int cands[4] = {-1, 2, 4, 6};
   int best = -2;
   for (int k = 0; k < 4; ++k) {
     const int l = cands[k];
-    if (!mapping_allowed(d, l)) continue;
+    if (!(l < 0 ? tpr : mapping_allowed(d, l))) continue;
     best = l;
     const int64_t lanes = (l < 0) ? n : (n << l);
-    if (lanes >= kTargetLanes) break;
+    if (lanes >= target) break;
   }
   return best;
 }
@@ -1055,7 +1086,7 @@ int choose_mapping(int d, int64_t n) {
 int rule_grid(int log2l, int64_t n, int d) {
   const int64_t per_block = log2l == kMapGk    ? kRuleBlockSize / gk_threads(d)
                             : log2l >= kMapR9 ? (kRuleBlockSize >> (log2l - kMapR9))
-                            : (log2l < 0)   ? kRuleBlockSize
+                            : (log2l < 0 || log2l == kMapR9Tpr) ? kRuleBlockSize
                                             : (kRuleBlockSize >> log2l);
   const int64_t g = (n + per_block - 1) / per_block;
   return (int)std::max<int64_t>(1, std::min<int64_t>(g, kMaxRuleGrid));
@@ -1192,8 +1223,12 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
   if (max_regions < n0) return GM_EINVAL;
   const int64_t cap = max_regions;
   const Layout lay = make_layout(d, cap);
-  // (the Gauss-Kronrod kernel has no factored form)
-  const int kfam = g_opt.rule == 1 ? fam : kernel_family(fam, d, params, lo, hi);
+  // (the Gauss-Kronrod kernel has no factored form, nor have several lanes per
+  // region, which the option can ask for, up to d = 10)
+  const bool chain = g_opt.rule == 1 || (g_opt.rule == 0 && d <= kTprMaxDim &&
+                                         g_opt.lanes_per_region > 1 &&
+                                         mapping_allowed(d, forced_log2l()));
+  const int kfam = chain ? fam : kernel_family(fam, d, params, lo, hi);
   g_last.valid = false;  // (before the workspace may move)
   char* base = fixed_base;
   int rc = GM_OK;
@@ -1321,7 +1356,7 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
     }
     int64_t nb = n;
     for (int k = 0; k < K; ++k) {
-      const int map = choose_mapping(d, nb);
+      const int map = choose_mapping(d, kfam, nb, false);
       const int rg = rule_grid(map, nb, d);
       const int tg = tile_grid_for(nb);
       g_stats.lanes_per_region = lanes_of_mapping(map, d);
@@ -1521,7 +1556,7 @@ int gm_eval_regions(int integrand_id, const double* params, int d, const double*
   GM_HIP(hipMemcpyAsync((void*)ra.C[0], cs.data(), sizeof(double) * d * n, hipMemcpyHostToDevice, s));
   GM_HIP(hipMemcpyAsync((void*)ra.H[0], hs.data(), sizeof(double) * d * n, hipMemcpyHostToDevice, s));
   GM_HIP(hipMemcpyAsync((void*)ra.L[0], ls.data(), sizeof(uint16_t) * n, hipMemcpyHostToDevice, s));
-  const int map = choose_mapping(d, n);
+  const int map = choose_mapping(d, integrand_id, n, true);
   // In chain form for every family: a region's err is a difference that a
   // resolved region cancels down to rounding, and a list's values are returned
   // one by one, so they keep the definition's order of operations (the launch is

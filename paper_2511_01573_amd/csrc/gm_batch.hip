@@ -792,7 +792,7 @@ int run_batch(int n, const int* fam, const double* params, const int* d, const d
     if (opt.rule != 0) {
       // degree 9 or Gauss-Kronrod: the kernel's own mapping, a fixed
       // grid-stride grid (items of d > 6 are invalid under Gauss-Kronrod)
-      rfn[g] = opt.rule == 2 ? r9_kernel(gd[g], gfam[g], true) : gk_kernel(gd[g], gfam[g], true);
+      rfn[g] = opt.rule == 2 ? r9_kernel(gd[g], gfam[g], true, rule9_log2l(gd[g])) : gk_kernel(gd[g], gfam[g], true);
       rgrid[g] = 2048;
     } else {
       const Tile t = tile_for(gd[g], base_family(gfam[g]));

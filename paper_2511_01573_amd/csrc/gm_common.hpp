@@ -316,7 +316,8 @@ RuleKernelFn rule_kernel_f4(int d, int log2l, bool batch);
 RuleKernelFn rule_kernel_f5(int d, int log2l, bool batch);
 RuleKernelFn rule_kernel_f6(int d, int log2l, bool batch);
 RuleKernelFn rule_kernel_f7(int d, int log2l, bool batch);
-// The same for the factored kernel families kOscF .. kDiscontinuousF (d >= kFactorMinDim).
+// The same for the factored kernel families kOscF .. kDiscontinuousF (d >=
+// kFactorMinDim): one lane at every d, several for d > kTprMaxDim.
 RuleKernelFn factor_kernel_f8(int d, int log2l, bool batch);
 RuleKernelFn factor_kernel_f9(int d, int log2l, bool batch);
 RuleKernelFn factor_kernel_f10(int d, int log2l, bool batch);
@@ -360,12 +361,14 @@ RuleKernelFn rule9_kernel_f4(int d, bool batch, bool wide);
 RuleKernelFn rule9_kernel_f5(int d, bool batch, bool wide);
 RuleKernelFn rule9_kernel_f6(int d, bool batch, bool wide);
 RuleKernelFn rule9_kernel_f7(int d, bool batch, bool wide);
-// The same for the factored kernel families (single store only).
-RuleKernelFn factor9_kernel_f8(int d, bool wide);
-RuleKernelFn factor9_kernel_f9(int d, bool wide);
-RuleKernelFn factor9_kernel_f10(int d, bool wide);
-RuleKernelFn factor9_kernel_f11(int d, bool wide);
-RuleKernelFn factor9_kernel_f12(int d, bool wide);
+// The same for the factored kernel families (single store only): one lane per
+// region (log2l < 0, d <= kTprMaxDim), rule9_log2l_wide(d) (d >= kTprMaxDim) or
+// rule9_log2l(d) (d > kTprMaxDim).
+RuleKernelFn factor9_kernel_f8(int d, int log2l);
+RuleKernelFn factor9_kernel_f9(int d, int log2l);
+RuleKernelFn factor9_kernel_f10(int d, int log2l);
+RuleKernelFn factor9_kernel_f11(int d, int log2l);
+RuleKernelFn factor9_kernel_f12(int d, int log2l);
 constexpr int rule9_log2l(int d) { return d - 5 < 2 ? 2 : (d - 5 > 6 ? 6 : d - 5); }
 // The wide mapping of the degree-9 kernel for active sets too small to fill
 // the GPU at rule9_log2l(d): up to 64 lanes per region (at least one corner

@@ -3,18 +3,21 @@
 // axis of gm_rule.hip (arXiv 2511.01573, Sec. 2) with the node values of
 // gm_nodes.hpp.
 //
-// Mappings, as in gm_rule.hip: one lane per region (TPR, d <= 10), everything
-// unrolled; or L = 2^l lanes of one wavefront per region (WPR), which form the
-// region's factors and partial products together in LDS, deal out the class 2-4
-// nodes as work items (an axis: 4 nodes and its fourth difference; an axis
-// pair: 4 nodes), sweep the corners behind their own signs of the first l
-// axes, and combine the class sums with shuffles.
+// Mappings.  One lane per region (TPR), everything unrolled but the corners'
+// outer loop: at d = 8 about 1800 FP64 operations a region, 950 of them the 56
+// exponentials of the Gaussian's factors (the chain form: 7600).  Above d = 10
+// also L = 2^l lanes of one wavefront per region (WPR), for sets too small to
+// fill the GPU: the lanes form the region's factors and partial products together
+// in LDS, deal out the class 2-4 nodes as work items (an axis: 4 nodes and its
+// fourth difference; an axis pair: 4 nodes), sweep the corners behind their own
+// signs of the first l axes, and combine the class sums with shuffles.  The
+// line between them: target_lanes in gm_api.hip.
 #include "gm_nodes.hpp"
 
 namespace gm {
 
 // ---------------------------------------------------------------------------
-// TPR: one lane per region (d <= 10).
+// TPR: one lane per region.
 // ---------------------------------------------------------------------------
 template <int D, int FAM>
 __device__ __forceinline__ RegionResult factor_region(const DevParams& P, const RuleConsts& K,
@@ -129,7 +132,7 @@ void factor_tpr_kernel(RuleArgs A) {
 }
 
 // ---------------------------------------------------------------------------
-// WPR: L = 2^LOG2L lanes per region.
+// WPR: L = 2^LOG2L lanes per region (d > 10).
 // ---------------------------------------------------------------------------
 // LDS per region: the factors of every axis at +-l2, +-l3, +-l5 and the centre,
 // the products of the centre factors before and after each axis, and the
@@ -143,7 +146,7 @@ struct FactorSlot {
   double dv[D], sc[D];
 };
 
-template <int D, int FAM, int LOG2L, bool BATCH>
+template <int D, int FAM, int LOG2L>
 __global__ __launch_bounds__(kRuleBlock) void factor_wpr_kernel(RuleArgs A) {
   using F = Alg<FAM>;
   using T = typename F::T;
@@ -154,8 +157,8 @@ __global__ __launch_bounds__(kRuleBlock) void factor_wpr_kernel(RuleArgs A) {
   __shared__ FactorSlot<D, FAM> slots[RPB];
   int64_t start, n;
   int buf;
-  if (!active_range<BATCH>(A, start, n, buf)) return;
-  const RegionSrc R = region_src<BATCH>(A, buf);
+  if (!active_range<false>(A, start, n, buf)) return;
+  const RegionSrc R = region_src<false>(A, buf);
   const RuleConsts& K = A.K;
   const int g = threadIdx.x >> LOG2L;  // region slot in the block
   const int s = threadIdx.x & (L - 1);
@@ -166,7 +169,7 @@ __global__ __launch_bounds__(kRuleBlock) void factor_wpr_kernel(RuleArgs A) {
     const int64_t r = rb + g;
     const bool valid = r < n;
     double volo;
-    const DevParams& P = region_params<BATCH>(A, buf, valid ? r : start, volo);
+    const DevParams& P = region_params<false>(A, buf, valid ? r : start, volo);
     double c[D], h[D];
     int lvl = 0;
     if (valid) {
@@ -296,7 +299,7 @@ __global__ __launch_bounds__(kRuleBlock) void factor_wpr_kernel(RuleArgs A) {
     }
     __syncthreads();
   }
-  if constexpr (!BATCH) block_partials(A, qs, es, nonfin);
+  block_partials(A, qs, es, nonfin);
 }
 
 // ---------------------------------------------------------------------------
@@ -313,16 +316,11 @@ static RuleKernelFn pick(int log2l) {
   if constexpr (B && (D < kBatchFactorMinDim || D > kBatchMaxDim)) {
     return nullptr;
   } else {
-    if (log2l < 0) {
-      if constexpr (D <= kTprMaxDim) return factor_tpr_kernel<D, F, B>;
-      return nullptr;
-    }
-    if (log2l == 2) return factor_wpr_kernel<D, F, 2, B>;
-    if constexpr (D >= 8) {
-      if (log2l == 4) return factor_wpr_kernel<D, F, 4, B>;
-    }
-    if constexpr (D >= 10) {
-      if (log2l == 6) return factor_wpr_kernel<D, F, 6, B>;
+    if (log2l < 0) return factor_tpr_kernel<D, F, B>;
+    if constexpr (D > kTprMaxDim) {
+      if (log2l == 2) return factor_wpr_kernel<D, F, 2>;
+      if (log2l == 4) return factor_wpr_kernel<D, F, 4>;
+      if (log2l == 6) return factor_wpr_kernel<D, F, 6>;
     }
     return nullptr;
   }

@@ -61,13 +61,15 @@ int validate(int fam, const double* params, int d, const double* lo, const doubl
 // these parameters on [lo, hi] in an adaptive run.
 int kernel_family(int fam, int d, const double* params, const double* lo, const double* hi);
 hipError_t launch_rule(int d, int fam, int log2l, const RuleArgs& a, int grid, hipStream_t s);
-// Rule-kernel mapping for n regions of dimension d: -1 = one lane per region,
-// else log2 of the lanes per region.
-int choose_mapping(int d, int64_t n);
+// Rule-kernel mapping for n regions of dimension d and kernel family kfam: -1 =
+// one lane per region, else log2 of the lanes per region (list: of a caller's
+// region list).
+int choose_mapping(int d, int kfam, int64_t n, bool list);
 RuleKernelFn rule_kernel(int d, int fam, int log2l, bool batch);
-// Degree-9 rule kernel of (d, family): single-store or batch-store variant;
-// `wide`: the single-store kernel with 2^rule9_log2l_wide(d) lanes per region.
-RuleKernelFn r9_kernel(int d, int fam, bool batch, bool wide = false);
+// Degree-9 rule kernel of (d, kernel family) with 2^log2l lanes per region
+// (rule9_log2l(d) or rule9_log2l_wide(d); factored families also one lane, log2l
+// < 0): single-store or batch-store variant.
+RuleKernelFn r9_kernel(int d, int fam, bool batch, int log2l);
 // Gauss-Kronrod rule kernel of (d, family), d <= kGkMaxDim.
 RuleKernelFn gk_kernel(int d, int fam, bool batch);
 // Nodes of the rule the options select.
