@@ -14,7 +14,7 @@ then the compact headline as the LAST line (well under 4 KB), holding
                     algorithmic FP64 FLOPs (evals x FLOPs per evaluation of
                     the family as implemented) / rule-kernel device time
                     measured with HIP events on the launch stream;
-  split_compaction  classify + scan + scatter against the HBM peak;
+  split_compaction  classify + scan + kept list against the HBM peak;
   cpu_baseline      the CPU oracle on a bounded sample of the workload;
   batch, grad, ...  one-number summaries of the modes against
                     one-call-per-integral;
@@ -508,14 +508,14 @@ def run_only(gm, W, mode: str, grad_tau: float, grad_cap: int, grad_rule: int):
 
 
 def split_compaction(gm, cases):
-    """HBM rate of classify + split/compaction (scan and scatter) over one pass
-    of the suite, timed per phase with HIP events on the launch stream
-    (option timing = 2; a pass of its own, outside the timed steps).
-    Algorithmic bytes: classify reads err, the level (one byte per region: two
-    children share their parent's) and the axis byte and writes the flag
-    (11 B per region) and reads Q of every retired region (8 B); the scatter
-    reads the flag and the axis byte (2 B per region) and, per kept region,
-    reads its parent record and writes its own (2 x (16d + 3) B)."""
+    """HBM rate of classify + compaction (scan and kept list) over one pass of the
+    suite, timed per phase with HIP events on the launch stream (option timing =
+    2; a pass of its own, outside the timed steps).  Algorithmic bytes: classify
+    reads err, the level (one byte per region: two children share their
+    parent's) and the axis byte and writes the flag (11 B per region) and reads Q
+    of every retired region (8 B); the list kernel reads the flag and the axis
+    byte (2 B per region) and writes 8 B per kept region.  The split regions'
+    records themselves move in the rule kernel."""
     gm.set_option("timing", 2)
     try:
         res = []
@@ -533,7 +533,7 @@ def split_compaction(gm, cases):
         n0 = 1 << (d * (12 // d))
         kept = (s["regions_evaluated"] - n0) // 2  # every split's two children were evaluated
         kept_total += kept
-        by += s["regions_evaluated"] * 13 + s["finished"] * 8 + kept * 2 * (16 * d + 3)
+        by += s["regions_evaluated"] * 13 + s["finished"] * 8 + kept * 8
         ms += s["classify_ms"] + s["split_ms"]
     return {"algorithmic_bytes": by, "kept_regions": kept_total, "device_ms": ms,
             "achieved_GBps": by / (ms * 1e-3) / 1e9, "peak_GBps": HBM_PEAK_GBPS,
@@ -659,11 +659,11 @@ def main():
     flops = sum(c["evals"] * FLOPS_PER_EVAL[c["family"]] for st in steps for c in st)
     launches = sum(c["rule_launches"] for st in steps for c in st)
     achieved = flops / rule_s / 1e12 if args.rule == 0 else None
-    # algorithmic HBM bytes per rule launch: per region half of the parent
-    # record two children share (8d + 1 B) read, Q, err and the axis byte (17 B)
-    # written
+    # algorithmic HBM bytes per rule launch: two children share a list entry (8 B)
+    # and the parent record (16d + 3 B) it points to, read, and their own parent
+    # record, written; Q, err and the axis byte (17 B) of each are written
     d = 8
-    alg_bytes = regions / launches * (8 * d + 1 + 17)
+    alg_bytes = regions / launches * (4 + 16 * d + 3 + 17)
     last = steps[-1]
     # time to tolerance of each integral: the median of its timed calls (the
     # warm-up calls load the code objects and size the workspace)

@@ -7,9 +7,13 @@
 //   classify  retire regions whose error share is negligible (+ guards),
 //             per-tile keep counts and retired partial sums
 //   scan      tile offsets of the kept regions; commit the retired sums
-//   scatter   halve every kept region along its axis into the other
-//             ping-pong buffer, stable order (child "-" at rank p, child "+"
-//             at n_keep + p); retired leaves appended in gradient mode
+//   list      the kept regions in stable order; the next iteration's rule
+//             kernel halves them along their axes (child "-" of entry p is
+//             region p, child "+" region n_keep + p); retired leaves appended
+//             in gradient mode
+//
+// Active sets of at most kStepRegions regions do everything after the rule in
+// one workgroup (step_kernel).
 //
 // All iteration state lives in a device Status block; kernels read the active
 // count and the ping-pong index from it and return at once when a final
@@ -40,8 +44,11 @@ constexpr int kTileThreads = 256;  // 4 regions per thread per tile
 constexpr int kMaxRuleGrid = 16384;
 constexpr int kPruneBins = 66;  // budget factors 2^1 .. 2^64, bin 65 = beyond
 constexpr int kMaxTileGrid = 8192;
-// Largest active set whose bookkeeping runs as one workgroup (small_step_kernel).
-constexpr int64_t kSmallStepRegions = 4 * 1024;
+// The one-workgroup bookkeeping kernel (step_kernel): its threads, and the
+// largest active set it takes.
+constexpr int kStepThreads = 1024;
+constexpr int kStepTiles = 32;
+constexpr int64_t kStepRegions = (int64_t)kStepTiles * kTile;
 
 struct InitArgs {
   double* C;
@@ -82,6 +89,12 @@ __device__ __forceinline__ void reduce_commit(Status* st, dd q, dd e, const dd* 
   e = dd_sum(e, dd{st->efin_hi, st->efin_lo});
   const double I = dd_val(q), E = dd_val(e);
   const int64_t n = st->n_active;
+  if (st->pending) {  // the rule kernel has written the set's records
+    st->pending = 0;
+    st->buf = 1 - st->buf;
+    st->split = 1;
+    st->n_par = st->n_keep;
+  }
   st->iter += 1;
   st->regions_evaluated += n;
   if (n > st->max_active) st->max_active = n;
@@ -106,33 +119,32 @@ __device__ __forceinline__ void reduce_commit(Status* st, dd q, dd e, const dd* 
 }
 
 // Global reduction of the rule kernel's block partials and the stopping rule
-// (the body of reduce_kernel and of the fused small-iteration kernel).  The
-// summation order is that of kReduceLanes virtual threads whatever the block
-// size (a divisor of kReduceLanes, a multiple of 64): virtual thread v adds
-// partials v, v + kReduceLanes, ..., the wavefronts' sums are combined in
-// order, so both kernels give the same bits.
+// (the body of reduce_kernel and of step_kernel, kReduceLanes threads): thread
+// v adds partials v, v + kReduceLanes, ..., the wavefronts' sums are combined
+// in order (those that had any; adding a zero sum changes nothing).
 constexpr int kReduceLanes = 1024;
 
 __device__ __forceinline__ void reduce_body(Status* st, const double* partials, int np,
                                             int64_t* hist) {
-  const int nthr = blockDim.x, tid = threadIdx.x;
-  for (int b = tid; b < kPruneBins; b += nthr) hist[b] = 0;
+  const int tid = threadIdx.x;
+  for (int b = tid; b < kPruneBins; b += kReduceLanes) hist[b] = 0;
   __shared__ dd sq[kReduceLanes / 64], se[kReduceLanes / 64];
-  for (int v = tid; v < kReduceLanes; v += nthr) {
+  const int nw = np >= kReduceLanes ? kReduceLanes / 64 : (np + 63) / 64;
+  if (tid < 64 * nw) {
     dd q = {0.0, 0.0}, e = {0.0, 0.0};
-    for (int p = v; p < np; p += kReduceLanes) {
+    for (int p = tid; p < np; p += kReduceLanes) {
       q = dd_sum(q, dd{partials[4 * p + 0], partials[4 * p + 1]});
       e = dd_sum(e, dd{partials[4 * p + 2], partials[4 * p + 3]});
     }
     q = wave_sum_dd(q);
     e = wave_sum_dd(e);
-    if ((v & 63) == 0) {
-      sq[v >> 6] = q;
-      se[v >> 6] = e;
+    if ((tid & 63) == 0) {
+      sq[tid >> 6] = q;
+      se[tid >> 6] = e;
     }
   }
   __syncthreads();
-  if (tid == 0) reduce_commit(st, sq[0], se[0], sq, se, kReduceLanes / 64);
+  if (tid == 0) reduce_commit(st, sq[0], se[0], sq, se, nw);
 }
 
 __global__ __launch_bounds__(1024) void reduce_kernel(Status* st, const double* partials, int np,
@@ -172,13 +184,16 @@ __device__ __forceinline__ int prune_level(double err, double T, int lvl) {
 // overflows the store the scan kernel picks the smallest sufficient factor
 // 2^k and the second pass (SECOND) classifies again with err <= T 2^(k - lvl)
 // added to the retire test.
-// The tiles tile0, tile0 + tstride, ... of the active set (the body of
-// classify_kernel, and of the fused small-iteration kernel with one block);
-// blocks of kTileThreads threads.
+// Blocks of kTileThreads threads, a tile at a time.
+__device__ __forceinline__ bool retires(double err, double T, double aI, int lvl, uint8_t ax) {
+  return (err <= ldexp(T, -lvl)) || (aI + err == aI) || (ax & kGeoBit);
+}
+
 template <bool SECOND>
-__device__ __forceinline__ void classify_tiles(const ClassifyArgs& A, int64_t tile0,
-                                               int64_t tstride) {
+__global__ __launch_bounds__(kTileThreads) void classify_kernel(ClassifyArgs A) {
   const Status* st = A.st;
+  if (st->done) return;
+  if (SECOND && !st->reclassify) return;
   const int64_t n = st->n_active;
   const double T = st->T;
   const double aI = fabs(st->I);
@@ -195,7 +210,7 @@ __device__ __forceinline__ void classify_tiles(const ClassifyArgs& A, int64_t ti
     for (int b = threadIdx.x; b < kPruneBins; b += kTileThreads) shist[b] = 0;
     __syncthreads();
   }
-  for (int64_t tile = tile0; tile < nt; tile += tstride) {
+  for (int64_t tile = blockIdx.x; tile < nt; tile += gridDim.x) {
     int64_t keep = 0;
     dd q = {0.0, 0.0}, e = {0.0, 0.0};
     // Every row's inputs are loaded first, by every lane (index clamped into
@@ -221,7 +236,7 @@ __device__ __forceinline__ void classify_tiles(const ClassifyArgs& A, int64_t ti
       if (r < n && GM_INB(r, st->cap)) {
         const double err = errv[k];
         const int lvl = lvlv[k] + (split ? 1 : 0);
-        bool fin = (err <= ldexp(T, -lvl)) || (aI + err == aI) || (axv[k] & 0x80);
+        bool fin = retires(err, T, aI, lvl, axv[k]);
         if (SECOND && !fin) fin = err <= ldexp(T, prune_k - lvl);
         if (hist_on && !fin) atomicAdd(&shist[prune_level(err, T, lvl)], 1u);
         A.FLAG[r] = fin ? 1 : 0;
@@ -265,13 +280,6 @@ __device__ __forceinline__ void classify_tiles(const ClassifyArgs& A, int64_t ti
   }
 }
 
-template <bool SECOND>
-__global__ __launch_bounds__(kTileThreads) void classify_kernel(ClassifyArgs A) {
-  if (A.st->done) return;
-  if (SECOND && !A.st->reclassify) return;
-  classify_tiles<SECOND>(A, blockIdx.x, gridDim.x);
-}
-
 // Exclusive scan of the per-tile keep counts (one workgroup), capacity and
 // precision checks, and the commit of the retired partial sums.  When the
 // kept set overflows the store and pruning is on, the first pass picks the
@@ -280,14 +288,14 @@ __global__ __launch_bounds__(kTileThreads) void classify_kernel(ClassifyArgs A) 
 template <bool SECOND>
 __device__ void scan_commit(Status* st, int64_t total, dd tq, dd te, const int64_t* HIST);
 
-// Exclusive scan of the tile counts by one block (the body of scan_kernel and
-// of the fused small-iteration kernel; any block size up to 1024 threads, a
-// multiple of 64): thread t takes `per` consecutive tiles.
+// Thread t takes `per` consecutive tiles.
 template <bool SECOND>
-__device__ __forceinline__ void scan_body(Status* st, const int64_t* TK, int64_t* TOFF,
-                                          const double* TQ, const double* TE,
-                                          const int64_t* HIST) {
-  const int nthr = blockDim.x;
+__global__ __launch_bounds__(1024) void scan_kernel(Status* st, const int64_t* TK, int64_t* TOFF,
+                                                    const double* TQ, const double* TE,
+                                                    const int64_t* HIST) {
+  if (st->done) return;
+  if (SECOND && !st->reclassify) return;
+  constexpr int nthr = 1024;
   const int64_t n = st->n_active;
   const int64_t nt = (n + kTile - 1) / kTile;
   const int64_t per = (nt + nthr - 1) / nthr;
@@ -338,15 +346,6 @@ __device__ __forceinline__ void scan_body(Status* st, const int64_t* TK, int64_t
   scan_commit<SECOND>(st, total, tq, te, HIST);
 }
 
-template <bool SECOND>
-__global__ __launch_bounds__(1024) void scan_kernel(Status* st, const int64_t* TK, int64_t* TOFF,
-                                                    const double* TQ, const double* TE,
-                                                    const int64_t* HIST) {
-  if (st->done) return;
-  if (SECOND && !st->reclassify) return;
-  scan_body<SECOND>(st, TK, TOFF, TQ, TE, HIST);
-}
-
 // Thread 0 of the scan: capacity and precision checks, the choice of the
 // pruning factor, the commit of the retired sums and the new active count.
 template <bool SECOND>
@@ -387,15 +386,13 @@ __device__ void scan_commit(Status* st, int64_t total, dd tq, dd te, const int64
   st->leaf_count += n - total;
   st->n_prev = n;
   st->n_keep = total;
-  st->split_in = st->split;
-  st->n_par_in = st->n_par;
   st->n_active = 2 * total;
-  st->n_par = total;
-  st->split = 1;
-  st->buf = 1 - st->buf;
+  st->pending = 1;
 }
 
-struct ScatterArgs {
+// The set being split, after the scan (records in `buf`, the kept list to the
+// other buffer), and the leaf store of gradient mode.
+struct ListArgs {
   Status* st;
   double* C[2];
   double* H[2];
@@ -404,166 +401,93 @@ struct ScatterArgs {
   int64_t cap;
   const uint8_t* AXIS;
   const uint8_t* FLAG;
-  int64_t* TOFF;
-  int d;
-  // gradient mode: retired leaves (SoA, capacity leaf_cap)
+  const int64_t* TOFF;
+  // retired leaves (SoA, capacity leaf_cap); null outside gradient mode
   double* LC;
   double* LH;
   uint16_t* LL;
   int64_t leaf_cap;
 };
 
-// Split + stable compaction (Sec. 3: filtering and splitting fused).  Ranks
-// inside a tile come from wavefront ballots and an LDS prefix over the four
-// wavefronts; the tile's base offset comes from the scan kernel.  Each kept
-// region is written once, at its rank p, as the record its two children are
-// read from in the next iteration (centre, half-widths, level and the split
-// axis the rule kernel chose); retired regions go to the leaf store in
-// gradient mode.  The dimension is a template parameter so every coordinate
-// load of a region is issued before its stores.  scatter_tiles takes the
-// visits tile0, tile0 + tstride, ... of its tile order (the body of
-// scatter_kernel and of the fused small-iteration kernel).
-template <int D, bool SPLIT>
-__device__ __forceinline__ void scatter_tiles_t(const ScatterArgs& A, int64_t tile0,
-                                                int64_t tstride) {
+// Kept region r with split axis `axis` as entry p of the kept list.  (p < cap /
+// 2 holds by the scan's capacity check; the guard keeps the store inside the
+// list whatever the offsets hold.)
+__device__ __forceinline__ void list_kept(int64_t* idx, int64_t cap, int64_t p, int64_t r,
+                                          uint8_t axis) {
+  if (GM_GUARD(p, cap / 2)) idx[p] = (r << 8) | (axis & kAxisMask);
+}
+
+// Stable compaction (Sec. 3: filtering and splitting fused): the kept regions'
+// list.  Ranks inside a tile come from wavefront ballots and an LDS prefix over
+// the four wavefronts; the tile's base offset comes from the scan kernel.  D > 0
+// (gradient mode): the retired regions of dimension D are appended to the leaf
+// store as well; KEPT = false leaves the list alone (step_kernel has written it).
+// Without leaves it moves 2 B in and 8 B out per kept region, which at the sizes
+// that matter costs less than the launch (8 us at 10^6 regions).
+template <int D, bool KEPT>
+__global__ __launch_bounds__(kTileThreads) void list_kernel(ListArgs A) {
   const Status* st = A.st;
+  if (st->done) return;
   const int64_t n = st->n_prev;
-  const int out = st->buf, in = 1 - out;
+  const int in = st->buf;
   const int64_t leaf_base = st->leaf_base;
-  const RegionSrc R{A.C[in], A.H[in], A.L[in], A.PAX[in], A.cap, st->n_par_in, st->split_in};
-  double* __restrict__ Co = A.C[out];
-  double* __restrict__ Ho = A.H[out];
-  uint16_t* __restrict__ Lo = A.L[out];
-  uint8_t* __restrict__ Po = A.PAX[out];
   const int64_t cap = A.cap;
+  int64_t* __restrict__ idx = kept_list(A.C[1 - in], cap);
+  RegionSrc R{};
+  R.C = A.C[in];
+  R.H = A.H[in];
+  R.L = A.L[in];
+  R.PAX = A.PAX[in];
+  R.cap = cap;
+  R.npar = st->n_par;
+  R.split = st->split;
   const int64_t nt = (n + kTile - 1) / kTile;
-  // Visiting order: the children of parent q sit at q and q + n_par, in the
-  // first-half tile i and about the second-half tile m + i (m = the first
-  // half's tile count).  Visit v of the grid-stride loop takes the pair's two
-  // tiles at v = 16 (i / 8) + i % 8 and that + 8: blocks eight apart run on one
-  // XCD (workgroups go round-robin over the eight), so the parent records that
-  // the first tile reads are still in that XCD's L2 for the second.  Visits
-  // past either half's end do nothing.
-  const bool paired = SPLIT;
-  const int64_t m = paired ? (R.npar + kTile - 1) / kTile : nt;
-  const int64_t nv = paired ? 16 * ((m + 7) / 8) : nt;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  __shared__ int64_t wc[kTile / kTileThreads][kTileThreads / 64];
-  for (int64_t v = tile0; v < nv; v += tstride) {
-    int64_t tile = v;
-    if (paired) {
-      const int64_t u = v >> 3, i = (u >> 1) * 8 + (v & 7);
-      tile = (u & 1) ? m + i : i;
-      if ((u & 1) ? tile >= nt : i >= m) continue;  // uniform over the block
-    }
-    // The flags of the tile's rows and its offset are loaded together (one
-    // memory round trip), then the counts of every (row, wavefront), one
-    // barrier per tile.
-    constexpr int kRows = kTile / kTileThreads;
-    uint8_t fl[kRows];
+  constexpr int kRows = kTile / kTileThreads;
+  __shared__ int wc[kRows][kTileThreads / 64];
+  for (int64_t tile = blockIdx.x; tile < nt; tile += gridDim.x) {
+    // every row's flag and axis and the tile's offset in one memory round trip
+    uint8_t fl[kRows], ax[kRows];
 #pragma unroll
     for (int k = 0; k < kRows; ++k) {
-      const int64_t r = tile * kTile + k * kTileThreads + threadIdx.x;
-      fl[k] = A.FLAG[r < n ? r : n - 1];
+      const int64_t r0 = tile * kTile + k * kTileThreads + threadIdx.x;
+      const int64_t r = r0 < n ? r0 : n - 1;
+      fl[k] = A.FLAG[r];
+      ax[k] = A.AXIS[r];
     }
-    const int64_t tile_base = GM_INB(tile, (cap + kTile - 1) / kTile + 1) ? A.TOFF[tile] : 0;
-    bool keepv[kRows];
+    int64_t base = GM_INB(tile, (cap + kTile - 1) / kTile + 1) ? A.TOFF[tile] : 0;
     uint64_t masks[kRows];
 #pragma unroll
     for (int k = 0; k < kRows; ++k) {
       const int64_t r = tile * kTile + k * kTileThreads + threadIdx.x;
-      keepv[k] = (r < n) && (fl[k] == 0);
-      masks[k] = __ballot(keepv[k]);
+      masks[k] = __ballot(r < n && fl[k] == 0);
       if (lane == 0) wc[k][w] = __popcll(masks[k]);
     }
     __syncthreads();
-    // Destination of each row's region: rank p among the kept (parent
-    // record), else its slot in the leaf store (gradient mode); -1 = none.
-    // (p < cap / 2 holds by the scan's capacity check; the guards keep every
-    // store inside its buffer whatever the offsets hold.)
-    int64_t dst[kRows];
-    {
-      int64_t base = tile_base;
 #pragma unroll
-      for (int k = 0; k < kRows; ++k) {
-        const int64_t r = tile * kTile + k * kTileThreads + threadIdx.x;
-        int64_t off = base, rowtot = 0;
+    for (int k = 0; k < kRows; ++k) {
+      const int64_t r = tile * kTile + k * kTileThreads + threadIdx.x;
+      int64_t off = base;
 #pragma unroll
-        for (int i = 0; i < kTileThreads / 64; ++i) {
-          if (i < w) off += wc[k][i];
-          rowtot += wc[k][i];
-        }
-        const int64_t before = off + __popcll(masks[k] & ((1ull << lane) - 1ull));
-        if (keepv[k]) {
-          dst[k] = GM_GUARD(before, cap) ? before : -1;
-        } else {
-          const int64_t slot = leaf_base + (r - before);
-          dst[k] = (A.LC != nullptr && r < n && GM_GUARD(slot, A.leaf_cap)) ? slot : -1;
-        }
-        base += rowtot;
+      for (int i = 0; i < kTileThreads / 64; ++i) {
+        if (i < w) off += wc[k][i];
+        base += wc[k][i];
       }
-    }
-    // Records of kBatch rows are loaded before any of them is stored, so a
-    // wavefront has that many rows' reads in flight at once.
-    constexpr int kBatch = D <= 8 ? 4 : D <= 12 ? 2 : 1;
+      const int64_t before = off + __popcll(masks[k] & ((1ull << lane) - 1ull));
+      if ((masks[k] >> lane) & 1ull) {
+        if (KEPT) list_kept(idx, cap, before, r, ax[k]);
+      } else if (D > 0 && r < n) {
+        const int64_t slot = leaf_base + (r - before);
+        if (GM_GUARD(slot, A.leaf_cap)) {
+          constexpr int DD = D > 0 ? D : 1;
+          double c[DD], h[DD];
+          const int lvl = load_region<DD>(R, r, c, h);
 #pragma unroll
-    for (int k0 = 0; k0 < kRows; k0 += kBatch) {
-      // Every lane loads (the index clamped into the set), so no loaded
-      // value is merged across a branch before its use: the waits for a
-      // batch's loads come only at its stores.
-      double gc[kBatch][D], gh[kBatch][D];
-      uint16_t gl[kBatch];
-      uint8_t gp[kBatch], ga[kBatch];
-      bool gplus[kBatch];
-#pragma unroll
-      for (int b = 0; b < kBatch; ++b) {
-        const int64_t r0 = tile * kTile + (k0 + b) * kTileThreads + threadIdx.x;
-        const int64_t r = r0 < n ? r0 : n - 1;
-        gplus[b] = SPLIT && r >= R.npar;
-        int64_t q = gplus[b] ? r - R.npar : r;
-        if (!GM_INB(q, cap)) q = 0;
-#pragma unroll
-        for (int j = 0; j < D; ++j) {
-          gc[b][j] = R.C[j * cap + q];
-          gh[b][j] = R.H[j * cap + q];
-        }
-        gl[b] = R.L[q];
-        gp[b] = SPLIT ? R.PAX[q] : 0;
-        ga[b] = A.AXIS[r];
-      }
-#pragma unroll
-      for (int b = 0; b < kBatch; ++b) {
-        const int k = k0 + b;
-        const int64_t p = dst[k];
-        if (p < 0) continue;
-        // the child: the parent's split axis halved, the centre moved
-        double c[D], h[D];
-#pragma unroll
-        for (int j = 0; j < D; ++j) {
-          c[j] = gc[b][j];
-          h[j] = gh[b][j];
-          if (SPLIT && j == gp[b]) {
-            const double hp = gh[b][j] * 0.5;
-            c[j] = gplus[b] ? gc[b][j] + hp : gc[b][j] - hp;
-            h[j] = hp;
+          for (int j = 0; j < DD; ++j) {
+            A.LC[j * A.leaf_cap + slot] = c[j];
+            A.LH[j * A.leaf_cap + slot] = h[j];
           }
-        }
-        const int lvl = SPLIT ? gl[b] + 1 : gl[b];
-        if (keepv[k]) {
-#pragma unroll
-          for (int j = 0; j < D; ++j) {
-            Co[j * cap + p] = c[j];
-            Ho[j * cap + p] = h[j];
-          }
-          Lo[p] = (uint16_t)lvl;
-          Po[p] = ga[b] & kAxisMask;
-        } else {
-#pragma unroll
-          for (int j = 0; j < D; ++j) {
-            A.LC[j * A.leaf_cap + p] = c[j];
-            A.LH[j * A.leaf_cap + p] = h[j];
-          }
-          A.LL[p] = (uint16_t)lvl;
+          A.LL[slot] = (uint16_t)lvl;
         }
       }
     }
@@ -571,87 +495,157 @@ __device__ __forceinline__ void scatter_tiles_t(const ScatterArgs& A, int64_t ti
   }
 }
 
-// (SPLIT: the input set is stored as parent records, as after every
-// iteration but the first.)
-template <int D>
-__device__ __forceinline__ void scatter_tiles(const ScatterArgs& A, int64_t tile0,
-                                              int64_t tstride) {
-  if (A.st->split_in)
-    scatter_tiles_t<D, true>(A, tile0, tstride);
-  else
-    scatter_tiles_t<D, false>(A, tile0, tstride);
-}
-
-template <int D>
-__global__ __launch_bounds__(kTileThreads) void scatter_kernel(ScatterArgs A) {
-  if (A.st->done) return;
-  scatter_tiles<D>(A, blockIdx.x, gridDim.x);
-}
-
-// One iteration's bookkeeping for a small active set in a single workgroup:
-// the reduction and stopping rule, the classification, the scan and the
-// split + compaction of reduce_kernel, classify_kernel<false>, scan_kernel<false>
-// and scatter_kernel, in that order and with the same results, separated by
-// workgroup barriers instead of kernel boundaries (for active sets of a few
-// tiles the four launches cost more than their work).  Not for memory-
-// pressure pruning (its second classification pass).
-template <int D>
-__global__ __launch_bounds__(kTileThreads) void small_step_kernel(Status* st,
-                                                                  const double* partials, int np,
-                                                                  ClassifyArgs ca, ScatterArgs sa) {
-  if (st->done) return;
-  reduce_body(st, partials, np, ca.HIST);
+// One iteration's bookkeeping for an active set of at most kStepRegions regions
+// in a single workgroup: the reduction and stopping rule, the classification,
+// the scan and the kept list of reduce_kernel, classify_kernel<false>,
+// scan_kernel<false> and list_kernel, in that order and with the same results
+// bit for bit, separated by workgroup barriers instead of kernel boundaries.
+// The four launches cost 4 to 8 us each for such sets, almost all of it launch
+// and memory latency: here the status block lives in LDS, a group of
+// kTileThreads threads takes a tile (four at a time), and the counts, ranks and
+// tile sums never leave the workgroup.  Not for memory-pressure pruning (its
+// second classification pass).  In gradient mode (ca.FLAG used by list_kernel
+// for the retired leaves) the flags and tile offsets are stored too.
+__global__ __launch_bounds__(kStepThreads) void step_kernel(Status* st, const double* partials,
+                                                            int np, ClassifyArgs ca, ListArgs la,
+                                                            int64_t* TOFF) {
+  constexpr int kWords = sizeof(Status) / 8;
+  constexpr int kGroups = kStepThreads / kTileThreads;  // tiles at a time
+  constexpr int kRows = kTile / kTileThreads;
+  constexpr int kTrips = kStepTiles / kGroups;
+  constexpr int kWaves = kTileThreads / 64;  // wavefronts of a group
+  static_assert(sizeof(Status) % 8 == 0 && kWords <= kStepThreads, "status words");
+  __shared__ Status ss;
+  __shared__ int cnt[kStepTiles][kRows][kWaves];
+  __shared__ dd sq[kStepTiles][kWaves], se[kStepTiles][kWaves];
+  __shared__ int64_t toff[kStepTiles];
+  const int tid = threadIdx.x, lane = tid & 63;
+  if (tid < kWords) ((int64_t*)&ss)[tid] = ((const int64_t*)st)[tid];
   __syncthreads();
-  if (st->done) return;
-  classify_tiles<false>(ca, 0, 1);
+  if (ss.done) return;
+  reduce_body(&ss, partials, np, ca.HIST);
   __syncthreads();
-  scan_body<false>(st, ca.TK, sa.TOFF, ca.TQ, ca.TE, ca.HIST);
-  __syncthreads();
-  if (st->done) return;
-  scatter_tiles<D>(sa, 0, 1);
-}
-
-using ScatterFn = void (*)(ScatterArgs);
-using SmallStepFn = void (*)(Status*, const double*, int, ClassifyArgs, ScatterArgs);
-
-static ScatterFn scatter_fn(int d) {
-  switch (d) {
-    case 2: return scatter_kernel<2>;
-    case 3: return scatter_kernel<3>;
-    case 4: return scatter_kernel<4>;
-    case 5: return scatter_kernel<5>;
-    case 6: return scatter_kernel<6>;
-    case 7: return scatter_kernel<7>;
-    case 8: return scatter_kernel<8>;
-    case 9: return scatter_kernel<9>;
-    case 10: return scatter_kernel<10>;
-    case 11: return scatter_kernel<11>;
-    case 12: return scatter_kernel<12>;
-    case 13: return scatter_kernel<13>;
-    case 14: return scatter_kernel<14>;
-    case 15: return scatter_kernel<15>;
-    case 16: return scatter_kernel<16>;
-    default: return nullptr;
+  const int64_t n = ss.n_active;
+  const int g = tid / kTileThreads, gt = tid % kTileThreads, w = gt >> 6;
+  const int nt = (int)((n + kTile - 1) / kTile);
+  uint32_t keepbits = 0;  // bit trip * kRows + row
+  if (!ss.done) {
+    const double T = ss.T, aI = fabs(ss.I);
+    const uint16_t* __restrict__ L = ca.L[ss.buf];
+    const int split = ss.split;
+    const int64_t npar = ss.n_par;
+    for (int trip = 0; trip < kTrips; ++trip) {
+      const int tile = trip * kGroups + g;
+      if (tile >= nt) break;
+      double errv[kRows], qv[kRows];
+      int lvlv[kRows];
+      uint8_t axv[kRows];
+#pragma unroll
+      for (int k = 0; k < kRows; ++k) {
+        const int64_t r = (int64_t)tile * kTile + k * kTileThreads + gt;
+        const int64_t rc = r < n ? r : n - 1;
+        errv[k] = ca.ERR[rc];
+        qv[k] = ca.Q[rc];
+        axv[k] = ca.AXIS[rc];
+        lvlv[k] = L[(split && rc >= npar) ? rc - npar : rc] + (split ? 1 : 0);
+      }
+      dd q = {0.0, 0.0}, e = {0.0, 0.0};
+#pragma unroll
+      for (int k = 0; k < kRows; ++k) {
+        const int64_t r = (int64_t)tile * kTile + k * kTileThreads + gt;
+        bool keep = false;
+        if (r < n && GM_INB(r, ss.cap)) {
+          const bool fin = retires(errv[k], T, aI, lvlv[k], axv[k]);
+          keep = !fin;
+          if (la.LC != nullptr) ca.FLAG[r] = fin ? 1 : 0;
+          if (fin) {
+            dd_add(q, qv[k]);
+            dd_add(e, errv[k]);
+          }
+        }
+        if (keep) keepbits |= 1u << (trip * kRows + k);
+        const uint64_t mask = __ballot(keep);
+        if (lane == 0) cnt[tile][k][w] = __popcll(mask);
+      }
+      q = wave_sum_dd(q);
+      e = wave_sum_dd(e);
+      if (lane == 0) {
+        sq[tile][w] = q;
+        se[tile][w] = e;
+      }
+    }
   }
+  __syncthreads();
+  if (!ss.done && tid < 64) {
+    // a lane per tile: its count and retired sums, then the scan over the tiles
+    int64_t sum = 0;
+    dd q = {0.0, 0.0}, e = {0.0, 0.0};
+    if (lane < nt) {
+#pragma unroll
+      for (int k = 0; k < kRows; ++k)
+#pragma unroll
+        for (int i = 0; i < kWaves; ++i) sum += cnt[lane][k][i];
+      dd tq = sq[lane][0], te = se[lane][0];
+#pragma unroll
+      for (int i = 1; i < kWaves; ++i) {
+        tq = dd_sum(tq, sq[lane][i]);
+        te = dd_sum(te, se[lane][i]);
+      }
+      q = dd_sum(q, tq);
+      e = dd_sum(e, te);
+    }
+    int64_t inc = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int64_t y = __shfl_up(inc, o, 64);
+      if (lane >= o) inc += y;
+    }
+    if (lane < nt) {
+      toff[lane] = inc - sum;
+      if (la.LC != nullptr && GM_INB(lane, (ss.cap + kTile - 1) / kTile + 1)) TOFF[lane] = inc - sum;
+    }
+    q = wave_sum_dd(q);
+    e = wave_sum_dd(e);
+    const int64_t total = __shfl(inc, 63, 64);
+    if (lane == 0) scan_commit<false>(&ss, total, q, e, ca.HIST);
+  }
+  __syncthreads();
+  if (!ss.done) {
+    int64_t* __restrict__ idx = kept_list(la.C[1 - ss.buf], la.cap);
+    for (int trip = 0; trip < kTrips; ++trip) {
+      const int tile = trip * kGroups + g;
+      if (tile >= nt) break;
+      int64_t base = toff[tile];
+#pragma unroll
+      for (int k = 0; k < kRows; ++k) {
+        const int64_t r = (int64_t)tile * kTile + k * kTileThreads + gt;
+        const bool keep = (keepbits >> (trip * kRows + k)) & 1u;
+        const uint64_t mask = __ballot(keep);
+        int64_t off = base;
+#pragma unroll
+        for (int i = 0; i < kWaves; ++i) {
+          if (i < w) off += cnt[tile][k][i];
+          base += cnt[tile][k][i];
+        }
+        if (keep)
+          list_kept(idx, la.cap, off + __popcll(mask & ((1ull << lane) - 1ull)), r, ca.AXIS[r]);
+      }
+    }
+  }
+  if (tid < kWords) ((int64_t*)st)[tid] = ((const int64_t*)&ss)[tid];
 }
 
-static SmallStepFn small_step_fn(int d) {
+using ListFn = void (*)(ListArgs);
+
+// The gradient mode's leaf store wants the dimension (kept: the list as well).
+static ListFn leaf_list_fn(int d, bool kept) {
   switch (d) {
-    case 2: return small_step_kernel<2>;
-    case 3: return small_step_kernel<3>;
-    case 4: return small_step_kernel<4>;
-    case 5: return small_step_kernel<5>;
-    case 6: return small_step_kernel<6>;
-    case 7: return small_step_kernel<7>;
-    case 8: return small_step_kernel<8>;
-    case 9: return small_step_kernel<9>;
-    case 10: return small_step_kernel<10>;
-    case 11: return small_step_kernel<11>;
-    case 12: return small_step_kernel<12>;
-    case 13: return small_step_kernel<13>;
-    case 14: return small_step_kernel<14>;
-    case 15: return small_step_kernel<15>;
-    case 16: return small_step_kernel<16>;
+#define GM_LEAF_CASE(D) \
+  case D: return kept ? list_kernel<D, true> : list_kernel<D, false>;
+    GM_LEAF_CASE(2) GM_LEAF_CASE(3) GM_LEAF_CASE(4) GM_LEAF_CASE(5) GM_LEAF_CASE(6)
+    GM_LEAF_CASE(7) GM_LEAF_CASE(8) GM_LEAF_CASE(9) GM_LEAF_CASE(10) GM_LEAF_CASE(11)
+    GM_LEAF_CASE(12) GM_LEAF_CASE(13) GM_LEAF_CASE(14) GM_LEAF_CASE(15) GM_LEAF_CASE(16)
+#undef GM_LEAF_CASE
     default: return nullptr;
   }
 }
@@ -1097,14 +1091,6 @@ static int tile_grid_for(int64_t n) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(g, kMaxTileGrid));
 }
 
-// Grid of the split + compaction: its paired visiting order (scatter_tiles)
-// has up to 16 * ceil(ceil(n / 2 / kTile) / 8) visits for n regions.
-static int scatter_grid_for(int64_t n) {
-  const int64_t m = (n / 2 + kTile - 1) / kTile + 1;
-  const int64_t g = std::max<int64_t>((n + kTile - 1) / kTile, 16 * ((m + 7) / 8));
-  return (int)std::max<int64_t>(1, std::min<int64_t>(g, kMaxTileGrid));
-}
-
 // Leaf store of the gradient mode (SoA, grows on demand).
 struct LeafStore {
   double* C = nullptr;
@@ -1242,10 +1228,10 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
   fill_params(fam, d, params, ra.P);
   fill_consts(d, ra.K);
   for (int b = 0; b < 2; ++b) {
-    ra.C[b] = (const double*)(base + lay.C[b]);
-    ra.H[b] = (const double*)(base + lay.H[b]);
-    ra.L[b] = (const uint16_t*)(base + lay.L[b]);
-    ra.PAX[b] = (const uint8_t*)(base + lay.PAX[b]);
+    ra.C[b] = (double*)(base + lay.C[b]);
+    ra.H[b] = (double*)(base + lay.H[b]);
+    ra.L[b] = (uint16_t*)(base + lay.L[b]);
+    ra.PAX[b] = (uint8_t*)(base + lay.PAX[b]);
   }
   ra.cap = cap;
   ra.Q = (double*)(base + lay.Q);
@@ -1261,9 +1247,9 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
 
   InitArgs ia;
   std::memset(&ia, 0, sizeof ia);
-  ia.C = (double*)ra.C[0];
-  ia.H = (double*)ra.H[0];
-  ia.L = (uint16_t*)ra.L[0];
+  ia.C = ra.C[0];
+  ia.H = ra.H[0];
+  ia.L = ra.L[0];
   ia.cap = cap;
   ia.n0 = n0;
   ia.d = d;
@@ -1286,20 +1272,20 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
   ca.TE = (double*)(base + lay.TE);
   ca.HIST = (int64_t*)(base + lay.HIST);
 
-  ScatterArgs sa;
-  std::memset(&sa, 0, sizeof sa);
-  sa.st = st;
+  int64_t* const toff = (int64_t*)(base + lay.TOFF);
+  ListArgs la;
+  std::memset(&la, 0, sizeof la);
+  la.st = st;
   for (int b = 0; b < 2; ++b) {
-    sa.C[b] = (double*)ra.C[b];
-    sa.H[b] = (double*)ra.H[b];
-    sa.L[b] = (uint16_t*)ra.L[b];
-    sa.PAX[b] = (uint8_t*)ra.PAX[b];
+    la.C[b] = ra.C[b];
+    la.H[b] = ra.H[b];
+    la.L[b] = ra.L[b];
+    la.PAX[b] = ra.PAX[b];
   }
-  sa.cap = cap;
-  sa.AXIS = ra.AXIS;
-  sa.FLAG = ca.FLAG;
-  sa.TOFF = (int64_t*)(base + lay.TOFF);
-  sa.d = d;
+  la.cap = cap;
+  la.AXIS = ra.AXIS;
+  la.FLAG = ca.FLAG;
+  la.TOFF = toff;
 
   Status hst;
   std::memset(&hst, 0, sizeof hst);
@@ -1338,6 +1324,7 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
     for (auto& row : ev)
       for (auto& e : row) GM_HIP(hipEventCreate(&e));
 
+  const ListFn list_fn = keep_leaves ? leaf_list_fn(d, true) : list_kernel<0, true>;
   int64_t n = n0;
   int64_t leaves_have = 0;
   int64_t iter_done = 0;
@@ -1349,10 +1336,10 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
       // Room for every region of this iteration to retire.
       rc = leaf_reserve(d, leaves_have + n, leaves_have, s);
       if (rc != GM_OK) return rc;
-      sa.LC = g_leaves.C;
-      sa.LH = g_leaves.H;
-      sa.LL = g_leaves.L;
-      sa.leaf_cap = g_leaves.cap;
+      la.LC = g_leaves.C;
+      la.LH = g_leaves.H;
+      la.LL = g_leaves.L;
+      la.leaf_cap = g_leaves.cap;
     }
     int64_t nb = n;
     for (int k = 0; k < K; ++k) {
@@ -1363,10 +1350,14 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
       if (timing) GM_HIP(hipEventRecord(ev[k][0], s));
       GM_HIP(launch_rule(d, kfam, map, ra, rg, s));
       if (timing) GM_HIP(hipEventRecord(ev[k][1], s));
-      if (!g_opt.prune && !phases && nb <= kSmallStepRegions) {
-        hipLaunchKernelGGL(small_step_fn(d), dim3(1), dim3(kTileThreads), 0, s, st, ra.partials,
-                           rg, ca, sa);
+      if (!g_opt.prune && !phases && nb <= kStepRegions) {
+        hipLaunchKernelGGL(step_kernel, dim3(1), dim3(kStepThreads), 0, s, st, ra.partials, rg, ca,
+                           la, toff);
         GM_HIP(hipGetLastError());
+        if (keep_leaves) {
+          hipLaunchKernelGGL(leaf_list_fn(d, false), dim3(tg), dim3(kTileThreads), 0, s, la);
+          GM_HIP(hipGetLastError());
+        }
         nb = std::min<int64_t>(cap, 2 * nb);
         continue;
       }
@@ -1376,17 +1367,17 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
       hipLaunchKernelGGL(classify_kernel<false>, dim3(tg), dim3(kTileThreads), 0, s, ca);
       GM_HIP(hipGetLastError());
       if (phases) GM_HIP(hipEventRecord(ev[k][3], s));
-      hipLaunchKernelGGL(scan_kernel<false>, dim3(1), dim3(1024), 0, s, st, ca.TK, sa.TOFF, ca.TQ,
+      hipLaunchKernelGGL(scan_kernel<false>, dim3(1), dim3(1024), 0, s, st, ca.TK, toff, ca.TQ,
                          ca.TE, ca.HIST);
       GM_HIP(hipGetLastError());
       if (g_opt.prune) {
         hipLaunchKernelGGL(classify_kernel<true>, dim3(tg), dim3(kTileThreads), 0, s, ca);
         GM_HIP(hipGetLastError());
-        hipLaunchKernelGGL(scan_kernel<true>, dim3(1), dim3(1024), 0, s, st, ca.TK, sa.TOFF, ca.TQ,
+        hipLaunchKernelGGL(scan_kernel<true>, dim3(1), dim3(1024), 0, s, st, ca.TK, toff, ca.TQ,
                            ca.TE, ca.HIST);
         GM_HIP(hipGetLastError());
       }
-      hipLaunchKernelGGL(scatter_fn(d), dim3(scatter_grid_for(nb)), dim3(kTileThreads), 0, s, sa);
+      hipLaunchKernelGGL(list_fn, dim3(tg), dim3(kTileThreads), 0, s, la);
       GM_HIP(hipGetLastError());
       if (phases) GM_HIP(hipEventRecord(ev[k][4], s));
       nb = std::min<int64_t>(cap, 2 * nb);
@@ -1540,9 +1531,9 @@ int gm_eval_regions(int integrand_id, const double* params, int d, const double*
   std::memset(&ra, 0, sizeof ra);
   fill_params(integrand_id, d, params, ra.P);
   fill_consts(d, ra.K);
-  ra.C[0] = ra.C[1] = (const double*)(base + lay.C[0]);
-  ra.H[0] = ra.H[1] = (const double*)(base + lay.H[0]);
-  ra.L[0] = ra.L[1] = (const uint16_t*)(base + lay.L[0]);
+  ra.C[0] = ra.C[1] = (double*)(base + lay.C[0]);
+  ra.H[0] = ra.H[1] = (double*)(base + lay.H[0]);
+  ra.L[0] = ra.L[1] = (uint16_t*)(base + lay.L[0]);
   ra.cap = cap;
   ra.Q = (double*)(base + lay.Q);
   ra.ERR = (double*)(base + lay.ERR);
@@ -1553,9 +1544,9 @@ int gm_eval_regions(int integrand_id, const double* params, int d, const double*
   for (int j = 0; j < d; ++j) vol = vol * (hi[j] - lo[j]);
   ra.vol_omega = vol;
   ra.n_fixed = n;
-  GM_HIP(hipMemcpyAsync((void*)ra.C[0], cs.data(), sizeof(double) * d * n, hipMemcpyHostToDevice, s));
-  GM_HIP(hipMemcpyAsync((void*)ra.H[0], hs.data(), sizeof(double) * d * n, hipMemcpyHostToDevice, s));
-  GM_HIP(hipMemcpyAsync((void*)ra.L[0], ls.data(), sizeof(uint16_t) * n, hipMemcpyHostToDevice, s));
+  GM_HIP(hipMemcpyAsync(ra.C[0], cs.data(), sizeof(double) * d * n, hipMemcpyHostToDevice, s));
+  GM_HIP(hipMemcpyAsync(ra.H[0], hs.data(), sizeof(double) * d * n, hipMemcpyHostToDevice, s));
+  GM_HIP(hipMemcpyAsync(ra.L[0], ls.data(), sizeof(uint16_t) * n, hipMemcpyHostToDevice, s));
   const int map = choose_mapping(d, integrand_id, n, true);
   // In chain form for every family: a region's err is a difference that a
   // resolved region cancels down to rounding, and a list's values are returned

@@ -65,7 +65,7 @@ void factor9_kernel(RuleArgs A) {
     double c[D], h[D];
     int lvl = 0;
     if (valid) {
-      lvl = load_region<D>(R, r, c, h);
+      lvl = load_active<D, L>(R, r, s, c, h);
     } else {
 #pragma unroll
       for (int j = 0; j < D; ++j) {
@@ -345,12 +345,12 @@ void factor9_tpr_kernel(RuleArgs A) {
   dd qs = {0.0, 0.0}, es = {0.0, 0.0};
   int nonfin = 0;
   // (siblings in neighbouring lanes, as in rule_tpr_kernel)
-  const bool pairs = R.split && end == 2 * R.npar;
+  const bool pairs = R.pending;
   int64_t v = start + (int64_t)blockIdx.x * kRuleBlock + threadIdx.x;
   for (; v < end; v += stride) {
-    const int64_t r = pairs ? ((v & 1) ? R.npar + (v >> 1) : (v >> 1)) : v;
+    const int64_t r = pairs ? ((v & 1) ? R.nkeep + (v >> 1) : (v >> 1)) : v;
     double c[D], h[D];
-    const int lvl = load_region<D>(R, r, c, h);
+    const int lvl = load_active<D, 1>(R, r, 0, c, h);
     const RegionResult o = factor9_region<D, FAM>(A.P, A.K, c, h, ldexp(A.vol_omega, -lvl));
     store_result(A, r, o);
     dd_add(qs, o.q);

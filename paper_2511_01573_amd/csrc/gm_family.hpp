@@ -249,12 +249,25 @@ __device__ __forceinline__ bool active_range(const RuleArgs& A, int64_t& start, 
 // the regions themselves).
 template <bool BATCH>
 __device__ __forceinline__ RegionSrc region_src(const RuleArgs& A, int buf) {
-  RegionSrc R{A.C[buf], A.H[buf], A.L[buf], nullptr, A.cap, 0, 0};
+  RegionSrc R{};
+  R.C = A.C[buf];
+  R.H = A.H[buf];
+  R.L = A.L[buf];
+  R.cap = A.cap;
   if constexpr (!BATCH) {
     if (A.n_fixed < 0 && A.st->split) {
       R.split = 1;
       R.npar = A.st->n_par;
       R.PAX = A.PAX[buf];
+    }
+    if (A.n_fixed < 0 && A.st->pending) {
+      R.pending = 1;
+      R.nkeep = A.st->n_keep;
+      R.Cw = A.C[1 - buf];
+      R.Hw = A.H[1 - buf];
+      R.Lw = A.L[1 - buf];
+      R.PAXw = A.PAX[1 - buf];
+      R.IDX = kept_list(R.Cw, A.cap);
     }
   }
   return R;

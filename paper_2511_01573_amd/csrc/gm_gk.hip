@@ -115,7 +115,7 @@ __global__ __launch_bounds__(kRuleBlock) void rule_gk_kernel(RuleArgs A) {
     double c[D], h[D];
     int lvl = 0;
     if (ok) {
-      lvl = load_region<D>(R, r, c, h);
+      lvl = load_active<D, NT>(R, r, t, c, h);
     } else {
 #pragma unroll
       for (int j = 0; j < D; ++j) {

@@ -109,12 +109,18 @@ extern "C" int gm_integrate_grad(int integrand_id, const double* params, int d, 
       if (part) (void)hipFree(part);
       return GM_ENOMEM;
     }
-    const RegionSrc leaves{lv.C, lv.H, lv.L, nullptr, lv.cap, 0, 0};
-    const RegionSrc active{(const double*)(rr.base + rr.lay.C[rr.buf]),
-                           (const double*)(rr.base + rr.lay.H[rr.buf]),
-                           (const uint16_t*)(rr.base + rr.lay.L[rr.buf]),
-                           (const uint8_t*)(rr.base + rr.lay.PAX[rr.buf]), rr.cap, rr.final_npar,
-                           rr.final_split};
+    RegionSrc leaves{}, active{};
+    leaves.C = lv.C;
+    leaves.H = lv.H;
+    leaves.L = lv.L;
+    leaves.cap = lv.cap;
+    active.C = (const double*)(rr.base + rr.lay.C[rr.buf]);
+    active.H = (const double*)(rr.base + rr.lay.H[rr.buf]);
+    active.L = (const uint16_t*)(rr.base + rr.lay.L[rr.buf]);
+    active.PAX = (const uint8_t*)(rr.base + rr.lay.PAX[rr.buf]);
+    active.cap = rr.cap;
+    active.npar = rr.final_npar;
+    active.split = rr.final_split;
     int64_t blk = 0;
     for (int pt = 0; pt < nparts; ++pt) {
       AdjFn fn = adj_fn(d, integrand_id, r9, parts[pt]);

@@ -151,15 +151,15 @@ void rule_tpr_kernel(RuleArgs A) {
   const int64_t stride = (int64_t)gridDim.x * kRuleBlock;
   dd qs = {0.0, 0.0}, es = {0.0, 0.0};
   int nonfin = 0;
-  // A split set holds the two children of parent q at q and q + n_par; lane
+  // A split set holds the two children of parent q at q and q + n_keep; lane
   // v takes child v & 1 of parent v >> 1, so siblings sit in neighbouring
-  // lanes and a wavefront reads each parent record once.
-  const bool pairs = R.split && end == 2 * R.npar;
+  // lanes and a wavefront reads (and writes) each parent record once.
+  const bool pairs = R.pending;
   int64_t v = start + (int64_t)blockIdx.x * kRuleBlock + threadIdx.x;
   for (; v < end; v += stride) {
-    const int64_t r = pairs ? ((v & 1) ? R.npar + (v >> 1) : (v >> 1)) : v;
+    const int64_t r = pairs ? ((v & 1) ? R.nkeep + (v >> 1) : (v >> 1)) : v;
     double c[D], h[D];
-    const int lvl = load_region<D>(R, r, c, h);
+    const int lvl = load_active<D, 1>(R, r, 0, c, h);
     double volo;
     const DevParams& P = region_params<BATCH>(A, buf, r, volo);
     const double vol = ldexp(volo, -lvl);
@@ -209,7 +209,7 @@ __global__ __launch_bounds__(kRuleBlock) void rule_wpr_kernel(RuleArgs A) {
     double c[D], h[D];
     int lvl = 0;
     if (valid) {
-      lvl = load_region<D>(R, r, c, h);
+      lvl = load_active<D, L>(R, r, s, c, h);
     } else {
 #pragma unroll
       for (int j = 0; j < D; ++j) {

@@ -84,7 +84,7 @@ void rule9_kernel(RuleArgs A) {
     double c[D], h[D];
     int lvl = 0;
     if (valid) {
-      lvl = load_region<D>(R, r, c, h);
+      lvl = load_active<D, L>(R, r, s, c, h);
     } else {
 #pragma unroll
       for (int j = 0; j < D; ++j) {
