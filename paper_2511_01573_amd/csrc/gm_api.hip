@@ -60,9 +60,17 @@ struct InitArgs {
   int m;  // cells per axis = 2^m
   double lo[kMaxDim];
   double half[kMaxDim];  // (hi - lo) / 2
+  Status* st;
+  Status status;  // the run's first status block
 };
 
+// Words of the status block (it is copied by the word).
+constexpr int kStatusWords = sizeof(Status) / 8;
+static_assert(sizeof(Status) % 8 == 0 && kStatusWords <= 64, "one wavefront copies the status");
+
+// Initial partition and status block.
 __global__ void init_kernel(InitArgs A) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *A.st = A.status;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const int64_t mask = ((int64_t)1 << A.m) - 1;
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < A.n0; t += stride) {
@@ -75,6 +83,31 @@ __global__ void init_kernel(InitArgs A) {
     }
     A.L[t] = (uint16_t)(A.m * A.d);
   }
+}
+
+// Host copies of the status block: the last kernel of an iteration stores the
+// block and then the iteration's number into a slot of pinned host memory that
+// the host reads, so a status read costs neither a copy nor a stream
+// synchronisation (together 12 to 20 us on the host, with the GPU idle behind
+// them).  Called by the whole first wavefront; the number is stored after the
+// words are visible to the host.
+struct alignas(256) StatusSlot {
+  int64_t words[kStatusWords];
+  int64_t seq;
+};
+struct Mirror {
+  StatusSlot* slot;  // null: the host copies the block itself
+  int64_t seq;
+};
+
+__device__ __forceinline__ void mirror_status(const Mirror& M, const Status* st) {
+  if (M.slot == nullptr) return;
+  if (threadIdx.x < kStatusWords)
+    __hip_atomic_store(&M.slot->words[threadIdx.x], ((const int64_t*)st)[threadIdx.x],
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __threadfence_system();
+  if (threadIdx.x == 0)
+    __hip_atomic_store(&M.slot->seq, M.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Thread 0 of the reduction: the waves' sums, the retired totals, the
@@ -425,8 +458,9 @@ __device__ __forceinline__ void list_kept(int64_t* idx, int64_t cap, int64_t p, 
 // Without leaves it moves 2 B in and 8 B out per kept region, which at the sizes
 // that matter costs less than the launch (8 us at 10^6 regions).
 template <int D, bool KEPT>
-__global__ __launch_bounds__(kTileThreads) void list_kernel(ListArgs A) {
+__global__ __launch_bounds__(kTileThreads) void list_kernel(ListArgs A, Mirror M) {
   const Status* st = A.st;
+  if (blockIdx.x == 0 && threadIdx.x < 64) mirror_status(M, st);
   if (st->done) return;
   const int64_t n = st->n_prev;
   const int in = st->buf;
@@ -508,19 +542,17 @@ __global__ __launch_bounds__(kTileThreads) void list_kernel(ListArgs A) {
 // for the retired leaves) the flags and tile offsets are stored too.
 __global__ __launch_bounds__(kStepThreads) void step_kernel(Status* st, const double* partials,
                                                             int np, ClassifyArgs ca, ListArgs la,
-                                                            int64_t* TOFF) {
-  constexpr int kWords = sizeof(Status) / 8;
+                                                            int64_t* TOFF, Mirror M) {
   constexpr int kGroups = kStepThreads / kTileThreads;  // tiles at a time
   constexpr int kRows = kTile / kTileThreads;
   constexpr int kTrips = kStepTiles / kGroups;
   constexpr int kWaves = kTileThreads / 64;  // wavefronts of a group
-  static_assert(sizeof(Status) % 8 == 0 && kWords <= kStepThreads, "status words");
   __shared__ Status ss;
   __shared__ int cnt[kStepTiles][kRows][kWaves];
   __shared__ dd sq[kStepTiles][kWaves], se[kStepTiles][kWaves];
   __shared__ int64_t toff[kStepTiles];
   const int tid = threadIdx.x, lane = tid & 63;
-  if (tid < kWords) ((int64_t*)&ss)[tid] = ((const int64_t*)st)[tid];
+  if (tid < kStatusWords) ((int64_t*)&ss)[tid] = ((const int64_t*)st)[tid];
   __syncthreads();
   if (ss.done) return;
   reduce_body(&ss, partials, np, ca.HIST);
@@ -632,10 +664,11 @@ __global__ __launch_bounds__(kStepThreads) void step_kernel(Status* st, const do
       }
     }
   }
-  if (tid < kWords) ((int64_t*)st)[tid] = ((const int64_t*)&ss)[tid];
+  if (tid < kStatusWords) ((int64_t*)st)[tid] = ((const int64_t*)&ss)[tid];
+  if (tid < 64) mirror_status(M, &ss);
 }
 
-using ListFn = void (*)(ListArgs);
+using ListFn = void (*)(ListArgs, Mirror);
 
 // The gradient mode's leaf store wants the dimension (kept: the list as well).
 static ListFn leaf_list_fn(int d, bool kept) {
@@ -1154,17 +1187,42 @@ static int leaf_reserve(int d, int64_t need, int64_t have, hipStream_t s) {
   return GM_OK;
 }
 
-// Pinned host copy of the status block: the host's status reads and the
-// initial write are direct DMA transfers instead of staged pageable copies.
-// create = false returns the copy only if an earlier call made it.
-static Status* pinned_status(bool create = true) {
-  static Status* p = nullptr;
-  if (!p && create &&
-      hipHostMalloc((void**)&p, sizeof(Status), hipHostMallocDefault) != hipSuccess) {
-    (void)hipGetLastError();
-    p = nullptr;
+// Pinned host slots of the status block (Mirror), one per iteration in flight.
+// create = false returns them only if an earlier call made them.
+constexpr int kMaxAhead = 8;
+constexpr int kSlots = 2 * kMaxAhead;
+static StatusSlot* status_slots(bool create) {
+  static StatusSlot* p = nullptr;
+  if (!p && create) {
+    if (hipHostMalloc((void**)&p, sizeof(StatusSlot) * kSlots,
+                      hipHostMallocPortable | hipHostMallocCoherent) != hipSuccess) {
+      (void)hipGetLastError();
+      p = nullptr;
+    } else {
+      std::memset((void*)p, 0, sizeof(StatusSlot) * kSlots);
+    }
   }
   return p;
+}
+static int64_t g_status_seq = 0;  // numbers the iterations of every run
+
+// Wait until the GPU has filled the slot for iteration number seq.  Ends with
+// an error if the stream drains or fails without it.
+static int await_slot(const StatusSlot* slot, int64_t seq, hipStream_t s, Status* out) {
+  for (int64_t spin = 1;; ++spin) {
+    if (__atomic_load_n(&slot->seq, __ATOMIC_ACQUIRE) == seq) break;
+    if ((spin & 0x3fff) == 0) {
+      const hipError_t e = hipStreamQuery(s);
+      if (e == hipSuccess && __atomic_load_n(&slot->seq, __ATOMIC_ACQUIRE) != seq) {
+        g_hip_err = "internal error: an iteration ended without a status";
+        return GM_EHIP;
+      }
+      if (e != hipSuccess && e != hipErrorNotReady) return hip_fail(e);
+      (void)hipGetLastError();
+    }
+  }
+  std::memcpy(out, slot->words, sizeof *out);
+  return GM_OK;
 }
 
 // Fixed device scratch of gm_integrate_noalloc (callers that cannot allocate):
@@ -1295,27 +1353,24 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
   hst.rel_tol = rel_tol;
   hst.abs_tol = abs_tol;
   hst.prune_on = g_opt.prune;
-  Status* const pin = pinned_status(fixed_base == nullptr);
-  if (pin) {
-    *pin = hst;
-    GM_HIP(hipMemcpyAsync(st, pin, sizeof hst, hipMemcpyHostToDevice, s));
-  } else {
-    GM_HIP(hipMemcpyAsync(st, &hst, sizeof hst, hipMemcpyHostToDevice, s));
-  }
+  ia.st = st;
+  ia.status = hst;
   {
     int g = (int)std::min<int64_t>((n0 + 255) / 256, 4096);
     hipLaunchKernelGGL(init_kernel, dim3(g), dim3(256), 0, s, ia);
     GM_HIP(hipGetLastError());
   }
 
-  // Iterations launched back to back before the host reads the status
-  // block (6 while the active set is below 2^16 regions, 3 below 2^20, 2
-  // above): kernels take the active count from the device and return at once
-  // after a final status, so launches past the end cost only their launch.
-  // Grids are sized for the largest count the iteration can have (n doubles
-  // at most per iteration).  Gradient mode checks every iteration (the leaf
-  // store grows on the host's side).
-  constexpr int kMaxAhead = 8;
+  // Kernels take the active count from the device and return at once after a
+  // final status, so iterations can be launched before the host knows that they
+  // are needed; grids are sized for the largest count one can have (n doubles at
+  // most per iteration).  The host reads each iteration's status from its slot
+  // and keeps `ahead` iterations in flight: two, so that the GPU never waits for
+  // the host (an iteration takes 15 us or more, a read and its launches 5), and
+  // at most one is launched in vain.  Gradient mode keeps one (the leaf store
+  // grows on the host's side).  Without slots (events to read, or none made on
+  // the no-allocation path) the host launches a few iterations and copies the
+  // status behind them: 6 below 2^16 active regions, 3 below 2^20, 2 above.
   hipEvent_t ev[kMaxAhead][5] = {};
   // (events are created per run: not on the no-allocation path)
   const bool timing = g_opt.timing != 0 && !fixed_base;  // rule kernel only
@@ -1323,16 +1378,20 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
   if (timing)
     for (auto& row : ev)
       for (auto& e : row) GM_HIP(hipEventCreate(&e));
+  StatusSlot* const slots = timing ? nullptr : status_slots(fixed_base == nullptr);
 
   const ListFn list_fn = keep_leaves ? leaf_list_fn(d, true) : list_kernel<0, true>;
-  int64_t n = n0;
+  int64_t n = n0;             // active regions of iteration `seen`
   int64_t leaves_have = 0;
-  int64_t iter_done = 0;
+  int64_t seen = 0, launched = 0;  // iterations whose status is known / launched
+  const int64_t seq0 = g_status_seq;
   for (;;) {
-    int K = 1;
-    if (!keep_leaves)
-      K = g_opt.graph_iters > 0 ? std::min(g_opt.graph_iters, kMaxAhead) : (n < (1 << 16) ? 6 : n < (1 << 20) ? 3 : 2);
-    if (keep_leaves) {
+    int ahead = 1;
+    if (!keep_leaves) {
+      if (g_opt.graph_iters > 0) ahead = std::min(g_opt.graph_iters, kMaxAhead);
+      else if (slots) ahead = 2;
+      else ahead = n < (1 << 16) ? 6 : n < (1 << 20) ? 3 : 2;
+    } else {
       // Room for every region of this iteration to retire.
       rc = leaf_reserve(d, leaves_have + n, leaves_have, s);
       if (rc != GM_OK) return rc;
@@ -1342,20 +1401,24 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
       la.leaf_cap = g_leaves.cap;
     }
     int64_t nb = n;
-    for (int k = 0; k < K; ++k) {
+    for (int64_t k = seen; k < launched; ++k) nb = std::min<int64_t>(cap, 2 * nb);
+    for (; launched < seen + ahead; ++launched) {
       const int map = choose_mapping(d, kfam, nb, false);
       const int rg = rule_grid(map, nb, d);
       const int tg = tile_grid_for(nb);
       g_stats.lanes_per_region = lanes_of_mapping(map, d);
-      if (timing) GM_HIP(hipEventRecord(ev[k][0], s));
+      hipEvent_t* const e = ev[launched % kMaxAhead];
+      const Mirror mir{slots ? slots + launched % kSlots : nullptr, ++g_status_seq};
+      if (timing) GM_HIP(hipEventRecord(e[0], s));
       GM_HIP(launch_rule(d, kfam, map, ra, rg, s));
-      if (timing) GM_HIP(hipEventRecord(ev[k][1], s));
+      if (timing) GM_HIP(hipEventRecord(e[1], s));
       if (!g_opt.prune && !phases && nb <= kStepRegions) {
         hipLaunchKernelGGL(step_kernel, dim3(1), dim3(kStepThreads), 0, s, st, ra.partials, rg, ca,
-                           la, toff);
+                           la, toff, mir);
         GM_HIP(hipGetLastError());
         if (keep_leaves) {
-          hipLaunchKernelGGL(leaf_list_fn(d, false), dim3(tg), dim3(kTileThreads), 0, s, la);
+          hipLaunchKernelGGL(leaf_list_fn(d, false), dim3(tg), dim3(kTileThreads), 0, s, la,
+                             Mirror{});
           GM_HIP(hipGetLastError());
         }
         nb = std::min<int64_t>(cap, 2 * nb);
@@ -1363,10 +1426,10 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
       }
       hipLaunchKernelGGL(reduce_kernel, dim3(1), dim3(1024), 0, s, st, ra.partials, rg, ca.HIST);
       GM_HIP(hipGetLastError());
-      if (phases) GM_HIP(hipEventRecord(ev[k][2], s));
+      if (phases) GM_HIP(hipEventRecord(e[2], s));
       hipLaunchKernelGGL(classify_kernel<false>, dim3(tg), dim3(kTileThreads), 0, s, ca);
       GM_HIP(hipGetLastError());
-      if (phases) GM_HIP(hipEventRecord(ev[k][3], s));
+      if (phases) GM_HIP(hipEventRecord(e[3], s));
       hipLaunchKernelGGL(scan_kernel<false>, dim3(1), dim3(1024), 0, s, st, ca.TK, toff, ca.TQ,
                          ca.TE, ca.HIST);
       GM_HIP(hipGetLastError());
@@ -1377,34 +1440,35 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
                            ca.TE, ca.HIST);
         GM_HIP(hipGetLastError());
       }
-      hipLaunchKernelGGL(list_fn, dim3(tg), dim3(kTileThreads), 0, s, la);
+      hipLaunchKernelGGL(list_fn, dim3(tg), dim3(kTileThreads), 0, s, la, mir);
       GM_HIP(hipGetLastError());
-      if (phases) GM_HIP(hipEventRecord(ev[k][4], s));
+      if (phases) GM_HIP(hipEventRecord(e[4], s));
       nb = std::min<int64_t>(cap, 2 * nb);
     }
-    GM_HIP(hipMemcpyAsync(pin ? (void*)pin : (void*)&hst, st, sizeof hst, hipMemcpyDeviceToHost, s));
-    GM_HIP(hipStreamSynchronize(s));
-    if (pin) hst = *pin;
-    const int ran = (int)std::min<int64_t>(K, hst.iter - iter_done);
-    if (ran <= 0 && !hst.done) {
+    const int64_t before = seen;
+    if (slots) {
+      rc = await_slot(slots + seen % kSlots, seq0 + seen + 1, s, &hst);
+      if (rc != GM_OK) return rc;
+      seen += 1;
+    } else {
+      GM_HIP(hipMemcpyAsync(&hst, st, sizeof hst, hipMemcpyDeviceToHost, s));
+      GM_HIP(hipStreamSynchronize(s));
+      seen = hst.done ? hst.iter : launched;
+    }
+    if (hst.iter < seen) {
       // the status block did not advance: never loop on it
       g_hip_err = "internal error: the device loop made no progress";
       return GM_EHIP;
     }
-    iter_done = hst.iter;
     if (timing) {
-      for (int k = 0; k < ran; ++k) {
-        float a = 0, b = 0, c = 0, e = 0;
-        GM_HIP(hipEventElapsedTime(&a, ev[k][0], ev[k][1]));
-        if (phases) {
-          GM_HIP(hipEventElapsedTime(&b, ev[k][1], ev[k][2]));
-          GM_HIP(hipEventElapsedTime(&c, ev[k][2], ev[k][3]));
-          GM_HIP(hipEventElapsedTime(&e, ev[k][3], ev[k][4]));
-        }
-        g_stats.rule_ms += a;
-        g_stats.reduce_ms += b;
-        g_stats.classify_ms += c;
-        g_stats.split_ms += e;
+      for (int64_t k = before; k < seen; ++k) {
+        hipEvent_t* const e = ev[k % kMaxAhead];
+        float t[4] = {0, 0, 0, 0};
+        for (int q = 0; q < (phases ? 4 : 1); ++q) GM_HIP(hipEventElapsedTime(&t[q], e[q], e[q + 1]));
+        g_stats.rule_ms += t[0];
+        g_stats.reduce_ms += t[1];
+        g_stats.classify_ms += t[2];
+        g_stats.split_ms += t[3];
         g_stats.rule_launches += 1;
       }
     }
@@ -1416,6 +1480,8 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
     if (hst.done) break;
     n = hst.n_active;
   }
+  // (an iteration launched in vain returns at once, but is part of this call)
+  if (slots) GM_HIP(hipStreamSynchronize(s));
   if (timing)
     for (auto& row : ev)
       for (auto& e : row) (void)hipEventDestroy(e);
