@@ -30,7 +30,7 @@ FAMILIES = range(1, 8)
 # translation units compiled once per integrand family (template-heavy kernels)
 PER_FAMILY = ("gm_rule", "gm_rule9", "gm_adjoint", "gm_gk")
 # ... and those compiled once per factored kernel family (gm_common.hpp kOscF ..)
-PER_FACTOR = ("gm_factor", "gm_factor9")
+PER_FACTOR = ("gm_factor", "gm_factor9", "gm_factor_adjoint")
 FACTOR_FAMILIES = range(8, 13)
 
 

@@ -30,4 +30,13 @@ AdjFn adjoint_kernel_f5(int d, bool r9, int part);
 AdjFn adjoint_kernel_f6(int d, bool r9, int part);
 AdjFn adjoint_kernel_f7(int d, bool r9, int part);
 
+// Factored adjoint kernels, one per factored kernel family (gm_common.hpp), for
+// kFactorMinDim <= d <= kAdjFactoredMaxDim: every class of the rule in one launch.
+constexpr int kAdjFactoredMaxDim = 10;
+AdjFn factor_adjoint_f8(int d, bool r9);
+AdjFn factor_adjoint_f9(int d, bool r9);
+AdjFn factor_adjoint_f10(int d, bool r9);
+AdjFn factor_adjoint_f11(int d, bool r9);
+AdjFn factor_adjoint_f12(int d, bool r9);
+
 }  // namespace gm

@@ -781,7 +781,7 @@ int check_bounds(int rc) {
   } units[] = {{"api", gm_check_poll_api}, {"batch", gm_check_poll_batch},
                {"grad", gm_check_poll_grad}, GM_POLL_F(rule), GM_POLL_F(rule9),
                GM_POLL_F(adjoint), GM_POLL_F(gk), GM_POLL_FACTOR(factor),
-               GM_POLL_FACTOR(factor9)};
+               GM_POLL_FACTOR(factor9), GM_POLL_FACTOR(factor_adjoint)};
 #undef GM_POLL_F
 #undef GM_POLL_FACTOR
   std::string first;

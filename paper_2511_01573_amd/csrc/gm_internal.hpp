@@ -115,6 +115,7 @@ GM_DECLARE_POLL_F(gk)
   int gm_check_poll_##name##_f12(CheckRec*);
 GM_DECLARE_POLL_FACTOR(factor)
 GM_DECLARE_POLL_FACTOR(factor9)
+GM_DECLARE_POLL_FACTOR(factor_adjoint)
 #undef GM_DECLARE_POLL_FACTOR
 #endif
 

@@ -113,3 +113,30 @@ def test_both_sides_of_the_line(fam, a, u, box):
     tol = 4.4e-13 if fam in (4, 5) else 1e-13
     assert np.all(np.abs(act["Q"][idx] - ref["Q"]) <= tol * np.maximum(np.abs(ref["Q"]), ref["scaleQ"]))
     assert np.all(np.abs(act["err"][idx] - ref["err"]) <= tol * ref["scaleE"])
+
+
+@pytest.mark.parametrize("rule", [0, 2])
+@pytest.mark.parametrize("d", [7, 8, 9, 10])
+@pytest.mark.parametrize("fam", FACTORED)
+def test_adjoint(fam, d, rule):
+    """The factored adjoint (d = 7..10) on a small tree with retired leaves and an
+    active set, against the oracle's node-by-node derivative sums: 1e-12 of the
+    largest component, as for every gradient (sums of the same nodes in another
+    grouping)."""
+    p = W.family_params(fam, d, seed=1100 + 10 * fam + d)
+    lo, hi = W.unit_box(d)
+    opts = {"max_iters": 3, "rule": rule, "init_log2_regions": d if d < 9 else 4}
+    for k, v in opts.items():
+        gm.set_option(k, v)
+    try:
+        print(f"case adjoint fam={fam} d={d} rule={rule}", flush=True)
+        I, _, g, st = gm.integrate_grad(fam, p, lo, hi, 1e-4, 1e-300, 1 << 16)
+    finally:
+        for k, v in {"max_iters": 10000, "rule": 0, "init_log2_regions": 12}.items():
+            gm.set_option(k, v)
+    ref = O.integrate_grad(fam, p, lo, hi, 1e-4, 1e-300, 1 << 16,
+                           init_log2=opts["init_log2_regions"], max_iters=3, rule_id=rule)
+    assert st == ref["status"]
+    assert abs(I - ref["I"]) <= 1e-12 * abs(ref["I"]) + 1e-300
+    scale = max(np.abs(ref["grad"]).max(), 1e-300)
+    assert np.abs(g - ref["grad"]).max() <= 1e-12 * scale, (g, ref["grad"])
