@@ -47,10 +47,11 @@ HBM_PEAK_GBPS = 8000.0
 # corner sweep of the one-lane-per-region kernel at d = 8 (256 of a region's 401
 # nodes), FMA = 2, ADD/MUL/RCP = 1, per corner: its share of the tables of
 # partial products (or of the chain additions), the outer function where a node
-# has one (corner peak, polynomial) and the accumulation.  A factored family's
-# node is one multiply-add (rotations: two); forming its factors once per region
-# (56 exponentials or 24 sine-cosine pairs at d = 8) is not counted.
-FLOPS_PER_EVAL = {1: 5.45, 2: 2.31, 3: 16.8125, 4: 2.31, 5: 2.31, 6: 2.31, 7: 8.5}
+# has one (polynomial; the corner peak's reciprocal shared by four) and the
+# accumulation.  A factored family's node is one multiply-add (rotations: two);
+# forming its factors once per region (56 exponentials or 24 sine-cosine pairs at
+# d = 8) is not counted.
+FLOPS_PER_EVAL = {1: 5.45, 2: 2.31, 3: 11.0625, 4: 2.31, 5: 2.31, 6: 2.31, 7: 8.5}
 
 # HBM traffic of the rule kernel, per launch, measured with rocprofv3 --pmc
 # (FETCH_SIZE and WRITE_SIZE, each scaled by what the counter reads for a

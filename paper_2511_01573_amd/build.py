@@ -32,6 +32,8 @@ PER_FAMILY = ("gm_rule", "gm_rule9", "gm_adjoint", "gm_gk")
 # ... and those compiled once per factored kernel family (gm_common.hpp kOscF ..)
 PER_FACTOR = ("gm_factor", "gm_factor9", "gm_factor_adjoint")
 FACTOR_FAMILIES = range(8, 13)
+# the corner peak's quotient form (kCornerPeakQ), in the degree-7 rule kernel
+EXTRA_FAMILIES = {"gm_rule": (13,)}
 
 
 def _units():
@@ -39,7 +41,8 @@ def _units():
     for src in sorted(glob.glob(os.path.join(CSRC, "*.hip"))):
         name = os.path.splitext(os.path.basename(src))[0]
         if name in PER_FAMILY or name in PER_FACTOR:
-            for f in (FAMILIES if name in PER_FAMILY else FACTOR_FAMILIES):
+            for f in (*(FAMILIES if name in PER_FAMILY else FACTOR_FAMILIES),
+                      *EXTRA_FAMILIES.get(name, ())):
                 units.append((src, os.path.join(BUILD, f"{name}_f{f}.o"),
                               [f"-DGM_RULE_FAMILY={f}", f"-DGM_FAMILY={f}"]))
         else:

@@ -781,7 +781,8 @@ int check_bounds(int rc) {
   } units[] = {{"api", gm_check_poll_api}, {"batch", gm_check_poll_batch},
                {"grad", gm_check_poll_grad}, GM_POLL_F(rule), GM_POLL_F(rule9),
                GM_POLL_F(adjoint), GM_POLL_F(gk), GM_POLL_FACTOR(factor),
-               GM_POLL_FACTOR(factor9), GM_POLL_FACTOR(factor_adjoint)};
+               GM_POLL_FACTOR(factor9), GM_POLL_FACTOR(factor_adjoint),
+               {"rule f13", gm_check_poll_rule_f13}};
 #undef GM_POLL_F
 #undef GM_POLL_FACTOR
   std::string first;
@@ -952,9 +953,24 @@ int validate(int fam, const double* params, int d, const double* lo, const doubl
 // stay below 100 and the paper's f2 below 16 per axis; its f4 (a = 25, u = 1/2)
 // passes the line from d = 4 on.  The rotations of the oscillatory family have
 // no such limit.
+// The corner peak's quotient form multiplies four powers (1 + s)^(d+1): 1 + s, by
+// its exact range over the box (it is linear in x), stays within 2^+-(250 / (d + 1)),
+// so products and quotients stay within 2^+-1000, and its terms are not so much
+// larger than it that their rounding could reach its sign.
 int kernel_family(int fam, int d, const double* params, const double* lo, const double* hi) {
   if (d < kFactorMinDim) return fam;
   if (fam == kOsc) return kOscF;
+  if (fam == kCornerPeak) {
+    double smin = 1.0, smax = 1.0, mag = 1.0;
+    for (int j = 0; j < d; ++j) {
+      const double p = params[j] * lo[j], q = params[j] * hi[j];
+      smin += std::min(p, q);
+      smax += std::max(p, q);
+      mag += std::max(std::fabs(p), std::fabs(q));
+    }
+    const double lim = std::exp2(250.0 / (d + 1));
+    return smin * lim >= 1.0 && smax <= lim && mag <= 0x1p40 * smin ? kCornerPeakQ : fam;
+  }
   if (fam != kProductPeak && fam != kGaussian && fam != kC0 && fam != kDiscontinuous) return fam;
   double span = 0.0;
   for (int j = 0; j < d; ++j) {
@@ -994,6 +1010,7 @@ RuleKernelFn rule_kernel(int d, int fam, int log2l, bool batch) {
     case kGaussianF: return factor_kernel_f10(d, log2l, batch);
     case kC0F: return factor_kernel_f11(d, log2l, batch);
     case kDiscontinuousF: return factor_kernel_f12(d, log2l, batch);
+    case kCornerPeakQ: return rule_kernel_f13(d, log2l, batch);
     default: return nullptr;
   }
 }
@@ -1016,7 +1033,8 @@ RuleKernelFn r9_kernel(int d, int fam, bool batch, int log2l) {
   switch (fam) {
     case 1: return rule9_kernel_f1(d, batch, wide);
     case 2: return rule9_kernel_f2(d, batch, wide);
-    case 3: return rule9_kernel_f3(d, batch, wide);
+    case 3:
+    case kCornerPeakQ: return rule9_kernel_f3(d, batch, wide);
     case 4: return rule9_kernel_f4(d, batch, wide);
     case 5: return rule9_kernel_f5(d, batch, wide);
     case 6: return rule9_kernel_f6(d, batch, wide);
@@ -1102,7 +1120,7 @@ static int64_t target_lanes(int d, bool factored) {
 constexpr int64_t r9_tpr_regions(int d) { return d < 10 ? 0 : 4096; }
 
 int choose_mapping(int d, int kfam, int64_t n, bool list) {
-  const bool factored = base_family(kfam) != kfam;
+  const bool factored = is_factored(kfam);
   if (g_opt.rule == 1) return kMapGk;
   if (g_opt.rule == 2) {
     if (factored && d <= kTprMaxDim && n >= r9_tpr_regions(d)) return kMapR9Tpr;
@@ -1289,10 +1307,10 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
   const Layout lay = make_layout(d, cap);
   // (the Gauss-Kronrod kernel has no factored form, nor have several lanes per
   // region, which the option can ask for, up to d = 10)
-  const bool chain = g_opt.rule == 1 || (g_opt.rule == 0 && d <= kTprMaxDim &&
-                                         g_opt.lanes_per_region > 1 &&
-                                         mapping_allowed(d, forced_log2l()));
-  const int kfam = chain ? fam : kernel_family(fam, d, params, lo, hi);
+  const bool lanes = g_opt.rule == 0 && d <= kTprMaxDim && g_opt.lanes_per_region > 1 &&
+                     mapping_allowed(d, forced_log2l());
+  int kfam = g_opt.rule == 1 ? fam : kernel_family(fam, d, params, lo, hi);
+  if (lanes && is_factored(kfam)) kfam = fam;
   g_last.valid = false;  // (before the workspace may move)
   char* base = fixed_base;
   int rc = GM_OK;

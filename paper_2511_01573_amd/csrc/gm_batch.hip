@@ -641,7 +641,7 @@ int run_batch(int n, const int* fam, const double* params, const int* d, const d
   std::vector<int> kfam(fam, fam + n);
   if (opt.rule == 0)
     for (int i : valid)
-      if (d[i] >= kBatchFactorMinDim)
+      if (d[i] >= kBatchFactorMinDim && fam[i] != kCornerPeak)
         kfam[i] = kernel_family(fam[i], d[i], params + poff[i], lo + boff[i], hi + boff[i]);
   // Group items by (d, kernel family), stable.
   std::stable_sort(valid.begin(), valid.end(), [&](int a, int b) {

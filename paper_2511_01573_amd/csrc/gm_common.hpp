@@ -92,7 +92,10 @@ enum Family : int {
   kProductPeakF = 9,
   kGaussianF = 10,
   kC0F = 11,
-  kDiscontinuousF = 12
+  kDiscontinuousF = 12,
+  // The corner peak with the nodes' reciprocals taken together (gm_family.hpp
+  // Fam::quad_sum; the host picks it, kernel_family).
+  kCornerPeakQ = 13
 };
 // The integrand family a kernel family evaluates.
 constexpr int base_family(int kfam) {
@@ -101,8 +104,11 @@ constexpr int base_family(int kfam) {
          : kfam == kGaussianF      ? kGaussian
          : kfam == kC0F            ? kC0
          : kfam == kDiscontinuousF ? kDiscontinuous
+         : kfam == kCornerPeakQ    ? kCornerPeak
                                    : kfam;
 }
+// Kernel families whose nodes are products of tabulated factors (gm_nodes.hpp).
+constexpr bool is_factored(int kfam) { return kfam >= kOscF && kfam <= kDiscontinuousF; }
 
 // Integrand parameters as the kernels consume them.  a, u are the caller's;
 // inv_a2 = 1/(a*a) (product peak) and c0 = 2*pi*u_0 (oscillatory) are formed
@@ -386,6 +392,7 @@ RuleKernelFn rule_kernel_f4(int d, int log2l, bool batch);
 RuleKernelFn rule_kernel_f5(int d, int log2l, bool batch);
 RuleKernelFn rule_kernel_f6(int d, int log2l, bool batch);
 RuleKernelFn rule_kernel_f7(int d, int log2l, bool batch);
+RuleKernelFn rule_kernel_f13(int d, int log2l, bool batch);  // d >= kFactorMinDim, runs
 // The same for the factored kernel families kOscF .. kDiscontinuousF (d >=
 // kFactorMinDim): one lane at every d, several for d > kTprMaxDim.
 RuleKernelFn factor_kernel_f8(int d, int log2l, bool batch);

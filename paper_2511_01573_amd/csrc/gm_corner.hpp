@@ -95,6 +95,15 @@ __device__ __forceinline__ void fourth_diff(const RuleConsts& K, double f0, doub
   sc = (fabs(fp2) + fabs(fm2) + 2.0 * fabs(f0)) + K.r7 * (fabs(fp3) + fabs(fm3) + 2.0 * fabs(f0));
 }
 
+// The same from the axis' pair sums of a positive integrand.
+__device__ __forceinline__ void fourth_diff_pairs(const RuleConsts& K, double f0, double f2,
+                                                  double f3, double& Dv, double& sc) {
+  const double A = f2 - 2.0 * f0;
+  const double B = f3 - 2.0 * f0;
+  Dv = fabs(A - B * K.r7);
+  sc = (f2 + 2.0 * f0) + K.r7 * (f3 + 2.0 * f0);
+}
+
 // Class sums of the degree-7 rule into the rule value and error estimate.
 __device__ __forceinline__ void rule_combine(const RuleConsts& K, double s1, double s2, double s3,
                                              double s4, double s5, double vol, RegionResult& r) {

@@ -103,6 +103,7 @@ int check_bounds(int rc);
   int gm_check_poll_##name##_f7(CheckRec*);
 int gm_check_poll_api(CheckRec*);
 int gm_check_poll_batch(CheckRec*);
+int gm_check_poll_rule_f13(CheckRec*);
 int gm_check_poll_grad(CheckRec*);
 GM_DECLARE_POLL_F(rule)
 GM_DECLARE_POLL_F(rule9)

@@ -80,11 +80,20 @@ __device__ __forceinline__ RegionResult rule_region_tpr(const DevParams& P, cons
       for (int k = i + 1; k < D; ++k) s = F::comb(s, tc[k]);
       a[q] = s;
     }
-    F::template outer_n<D, 4>(P, a, f);
-    ks_add(S2, f[0] + f[1]);
-    ks_add(S3, f[2] + f[3]);
     double sc;
-    fourth_diff(K, f0, f[0], f[1], f[2], f[3], Dv[i], sc);
+    if constexpr (F::kQuotient) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) f[q] = F::template cpk_power<D>(a[q]);
+      const double f2 = F::pair_sum(f[0], f[1]), f3 = F::pair_sum(f[2], f[3]);
+      ks_add(S2, f2);
+      ks_add(S3, f3);
+      fourth_diff_pairs(K, f0, f2, f3, Dv[i], sc);
+    } else {
+      F::template outer_n<D, 4>(P, a, f);
+      ks_add(S2, f[0] + f[1]);
+      ks_add(S3, f[2] + f[3]);
+      fourth_diff(K, f0, f[0], f[1], f[2], f[3], Dv[i], sc);
+    }
     scale = sc > scale ? sc : scale;
   }
   // Class 4 walks (i, j) with loop counters that are the same in every lane
@@ -92,8 +101,33 @@ __device__ __forceinline__ RegionResult rule_region_tpr(const DevParams& P, cons
   // are compensated at the level of small groups: the +-pair of each class 2/3
   // axis and the (at most 2(d-1)) nodes of one (i, sign_i) row of class 4 are
   // added plainly and each group sum enters the compensated total.
+  // (Quotient form: row i's four sign patterns of (i, j) together.)
 #pragma unroll GM_UNROLL_A4
   for (int i = 0; i < D - 1; ++i) {
+    if constexpr (F::kQuotient) {
+      double m[2], g = 0.0;
+#pragma unroll
+      for (int si = 0; si < 2; ++si) {
+        const double ti = si ? t3m[i] : t3p[i];
+        m[si] = (i == 0) ? ti : F::comb(pc[i], ti);
+      }
+#pragma unroll
+      for (int j = i + 1; j < D; ++j) {
+        double p[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          double s = F::comb(m[q >> 1], (q & 1) ? t3m[j] : t3p[j]);
+#pragma unroll
+          for (int k = j + 1; k < D; ++k) s = F::comb(s, tc[k]);
+          p[q] = F::template cpk_power<D>(s);
+        }
+        g = F::quad_sum(p, g);
+        m[0] = F::comb(m[0], tc[j]);
+        m[1] = F::comb(m[1], tc[j]);
+      }
+      ks_add(S4, g);
+      continue;
+    }
 #pragma unroll
     for (int si = 0; si < 2; ++si) {
       const double ti = si ? t3m[i] : t3p[i];
@@ -255,13 +289,22 @@ __global__ __launch_bounds__(kRuleBlock) void rule_wpr_kernel(RuleArgs A) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) a[q] = (i == 0) ? v[q] : F::comb(pci, v[q]);
         chain_from<D, FAM, 4>(a, tc, i + 1, D);
-        F::template outer_n<D, 4>(P, a, f);
-        ks_add(S2, f[0]);
-        ks_add(S2, f[1]);
-        ks_add(S3, f[2]);
-        ks_add(S3, f[3]);
         double dv, scv;
-        fourth_diff(K, f0, f[0], f[1], f[2], f[3], dv, scv);
+        if constexpr (F::kQuotient) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) f[q] = F::template cpk_power<D>(a[q]);
+          const double f2 = F::pair_sum(f[0], f[1]), f3 = F::pair_sum(f[2], f[3]);
+          ks_add(S2, f2);
+          ks_add(S3, f3);
+          fourth_diff_pairs(K, f0, f2, f3, dv, scv);
+        } else {
+          F::template outer_n<D, 4>(P, a, f);
+          ks_add(S2, f[0]);
+          ks_add(S2, f[1]);
+          ks_add(S3, f[2]);
+          ks_add(S3, f[3]);
+          fourth_diff(K, f0, f[0], f[1], f[2], f[3], dv, scv);
+        }
         sl.dv[i] = dv;
         sl.sc[i] = scv;
       } else {
@@ -281,9 +324,15 @@ __global__ __launch_bounds__(kRuleBlock) void rule_wpr_kernel(RuleArgs A) {
                        F::comb(m[1], tj[1])};
         chain_from<D, FAM, 4>(a, tc, j + 1, D);
         double f[4];
-        F::template outer_n<D, 4>(P, a, f);
+        if constexpr (F::kQuotient) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) ks_add(S4, f[q]);
+          for (int q = 0; q < 4; ++q) f[q] = F::template cpk_power<D>(a[q]);
+          ks_add(S4, F::quad_sum(f, 0.0));
+        } else {
+          F::template outer_n<D, 4>(P, a, f);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) ks_add(S4, f[q]);
+        }
       }
     }
     // Class 5: this lane's 2^(D - LOG2L) corners.
@@ -351,23 +400,26 @@ __global__ __launch_bounds__(kRuleBlock) void rule_wpr_kernel(RuleArgs A) {
 // for (-DGM_RULE_FAMILY=k; the build compiles one object per family).
 // ---------------------------------------------------------------------------
 #ifndef GM_RULE_FAMILY
-#error "compile with -DGM_RULE_FAMILY=<1..7>"
+#error "compile with -DGM_RULE_FAMILY=<1..7 or 13>"
 #endif
 
 template <int D, bool B>
 static RuleKernelFn pick(int log2l) {
   constexpr int F = GM_RULE_FAMILY;
-  if (log2l < 0) {
-    if constexpr (D <= kTprMaxDim) return rule_tpr_kernel<D, F, B>;
-    return nullptr;
-  }
-  if constexpr (D >= 6) {
-    if (log2l == 2) return rule_wpr_kernel<D, F, 2, B>;
-    if constexpr (D >= 8) {
-      if (log2l == 4) return rule_wpr_kernel<D, F, 4, B>;
+  // (the quotient form: runs of dimension >= kFactorMinDim)
+  if constexpr (!Fam<F>::kQuotient || (!B && D >= kFactorMinDim)) {
+    if (log2l < 0) {
+      if constexpr (D <= kTprMaxDim) return rule_tpr_kernel<D, F, B>;
+      return nullptr;
     }
-    if constexpr (D >= 10) {
-      if (log2l == 6) return rule_wpr_kernel<D, F, 6, B>;
+    if constexpr (D >= 6) {
+      if (log2l == 2) return rule_wpr_kernel<D, F, 2, B>;
+      if constexpr (D >= 8) {
+        if (log2l == 4) return rule_wpr_kernel<D, F, 4, B>;
+      }
+      if constexpr (D >= 10) {
+        if (log2l == 6) return rule_wpr_kernel<D, F, 6, B>;
+      }
     }
   }
   return nullptr;

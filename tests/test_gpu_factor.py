@@ -140,3 +140,35 @@ def test_adjoint(fam, d, rule):
     assert abs(I - ref["I"]) <= 1e-12 * abs(ref["I"]) + 1e-300
     scale = max(np.abs(ref["grad"]).max(), 1e-300)
     assert np.abs(g - ref["grad"]).max() <= 1e-12 * scale, (g, ref["grad"])
+
+
+@pytest.mark.parametrize("d,lanes", [(7, (0, 1, 4)), (8, (1, 4, 16)), (9, (0, 16)), (10, (1, 16, 64)),
+                                     (11, (4, 64)), (13, (4, 16)), (16, (16, 64))])
+def test_corner_quotient_mappings(d, lanes):
+    """The corner peak with four nodes to a reciprocal, at the edges of its mappings."""
+    p = W.family_params(3, d, seed=2100 + d)
+    lo, hi = W.unit_box(d)
+    for ln in lanes:
+        print(f"case corner d={d} lanes={ln}", flush=True)
+        act, chain = _stopped_run(3, p, lo, hi, 4 if d <= 11 else 3, lanes=ln)
+        _check(3, p, lo, hi, act, chain, 0, f"corner d{d} lanes{ln}")
+
+
+@pytest.mark.parametrize("a", [2.8e7, 3.0e7, -(1 - 2.0 ** -27) / 8, -(1 - 2.0 ** -29) / 8, -0.2])
+def test_corner_both_sides_of_the_line(a):
+    """1 + sum a_j x_j reaching up or down to either side of the quotient form's
+    range (2^+-27.8 at d = 8), and through zero.  Where it falls towards 0, the
+    smallest at a node is above 0.02, and the rounding of the d terms (2^-53 each)
+    is raised to the power d + 1: 72 2^-53 / 0.02 = 4e-13."""
+    d = 8
+    lo, hi = W.unit_box(d)
+    p = np.concatenate([np.full(d, a), np.zeros(d)])
+    print(f"case corner line a={a}", flush=True)
+    if a == -0.2:  # singular inside the box: reported as before
+        assert gm.integrate(3, p, lo, hi, 1e-12, 1e-300, 1 << 16)[2] == gm.NONFINITE
+        return
+    act, _ = _stopped_run(3, p, lo, hi, 2)
+    idx = np.unique(np.linspace(0, act["lvl"].size - 1, 40).astype(int))
+    ref = O.rule_many(3, p, act["c"][idx], act["h"][idx], act["lvl"][idx], 1.0)
+    assert np.all(np.abs(act["Q"][idx] - ref["Q"]) <= 4e-13 * np.maximum(np.abs(ref["Q"]), ref["scaleQ"]))
+    assert np.all(np.abs(act["err"][idx] - ref["err"]) <= 4e-13 * ref["scaleE"])
