@@ -39,7 +39,7 @@ namespace gm {
 // ---------------------------------------------------------------------------
 // Control kernels.
 // ---------------------------------------------------------------------------
-constexpr int kTile = 1024;        // regions per classify/scatter tile
+constexpr int kTile = 1024;        // regions per classify tile
 constexpr int kTileThreads = 256;  // 4 regions per thread per tile
 constexpr int kMaxRuleGrid = 16384;
 constexpr int kPruneBins = 66;  // budget factors 2^1 .. 2^64, bin 65 = beyond
@@ -1148,13 +1148,28 @@ int choose_mapping(int d, int kfam, int64_t n, bool list) {
   return best;
 }
 
-int rule_grid(int log2l, int64_t n, int d) {
+// The factored one-lane kernels read a region's record while they evaluate the one
+// before (load_record), so their workgroups stay and stride: two fit a CU, 512 in
+// all, and twice as many even out the end.  Before, one workgroup per 256 regions
+// waited for status, list and record in turn: d = 8 Gaussian at 1e-7, ms for 16384
+// workgroups / without the read ahead / 512 / 1024 / 2048: 3.74 / 3.82 / 3.45 /
+// 3.47 / 3.44, oscillatory 2.19 / 2.21 / 2.12 / 2.07 / 2.08; 3.24e6 regions in one
+// launch 259 -> 219 us.  The degree-9 kernel has no registers for a second record
+// and gains by the start alone (C0 1.22 / - / 1.18 / 1.20 / 1.21).  The chain
+// kernels spend far longer on a region and only lose by the uneven end (corner
+// peak 6.80 / - / 6.95 / 6.83 / 6.77), as do more than ten dimensions.
+static int max_rule_grid(int log2l, int d, int kfam) {
+  if (!is_factored(kfam) || d > kTprMaxDim) return kMaxRuleGrid;
+  return log2l == kMapR9Tpr ? 512 : log2l < 0 ? 1024 : kMaxRuleGrid;
+}
+
+int rule_grid(int log2l, int64_t n, int d, int kfam) {
   const int64_t per_block = log2l == kMapGk    ? kRuleBlockSize / gk_threads(d)
                             : log2l >= kMapR9 ? (kRuleBlockSize >> (log2l - kMapR9))
                             : (log2l < 0 || log2l == kMapR9Tpr) ? kRuleBlockSize
                                             : (kRuleBlockSize >> log2l);
   const int64_t g = (n + per_block - 1) / per_block;
-  return (int)std::max<int64_t>(1, std::min<int64_t>(g, kMaxRuleGrid));
+  return (int)std::max<int64_t>(1, std::min<int64_t>(g, max_rule_grid(log2l, d, kfam)));
 }
 
 static int tile_grid_for(int64_t n) {
@@ -1442,7 +1457,7 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
     for (int64_t k = seen; k < launched; ++k) nb = std::min<int64_t>(cap, 2 * nb);
     for (; launched < seen + ahead; ++launched) {
       const int map = choose_mapping(d, kfam, nb, false);
-      const int rg = rule_grid(map, nb, d);
+      const int rg = rule_grid(map, nb, d, kfam);
       const int tg = tile_grid_for(nb);
       g_stats.lanes_per_region = lanes_of_mapping(map, d);
       hipEvent_t* const e = ev[launched % kMaxAhead];
@@ -1658,7 +1673,7 @@ int gm_eval_regions(int integrand_id, const double* params, int d, const double*
   // resolved region cancels down to rounding, and a list's values are returned
   // one by one, so they keep the definition's order of operations (the launch is
   // 7% of the call: 18 of 277 us for 30011 regions at d = 7).
-  GM_HIP(launch_rule(d, integrand_id, map, ra, rule_grid(map, n, d), s));
+  GM_HIP(launch_rule(d, integrand_id, map, ra, rule_grid(map, n, d, integrand_id), s));
   int32_t* const aout = (int32_t*)hin;
   hipLaunchKernelGGL(list_out_kernel, dim3((unsigned)lg), dim3(256), 0, s, ra.AXIS, n, aout);
   GM_HIP(hipGetLastError());

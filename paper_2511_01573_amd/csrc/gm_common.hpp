@@ -296,23 +296,77 @@ __device__ __forceinline__ int load_region(const RegionSrc& R, int64_t r, double
 }
 
 // Region r of the active set for the rule kernels, which write the records of a
-// pending set.  L threads work on a region, this one is number t of them.  With
-// one lane per region the two siblings of a record sit in neighbouring lanes:
+// pending set: load_record reads what is stored, form_region makes the region of
+// it (two steps, so that a kernel can have the next region's loads under way while
+// it works on one).  L threads work on a region, this one is number t of them.
+// With one lane per region the two siblings of a record sit in neighbouring lanes:
 // the "-" child writes the centre, the "+" child the half-widths.
+template <int D>
+struct Record {
+  double c[D], h[D];
+  int64_t e;  // pending set: the kept list's entry
+  int lvl, ax;
+};
+
+// The kept list's entry of region r.
+__device__ __forceinline__ int64_t list_entry(const RegionSrc& R, int64_t r) {
+  if (!R.pending) return 0;
+  const int64_t p = r >= R.nkeep ? r - R.nkeep : r;
+  return GM_INB(p, R.cap / 2) ? R.IDX[p] : -1;
+}
+
+template <int D>
+__device__ __forceinline__ void load_record(const RegionSrc& R, int64_t r, int64_t e,
+                                            Record<D>& o) {
+  const int64_t a = R.pending ? e >> 8 : r;
+  const int64_t q = R.split && a >= R.npar ? a - R.npar : a;
+  o.e = e;
+  o.lvl = o.ax = 0;
+  if (!GM_INB(q, R.cap)) {
+#pragma unroll
+    for (int j = 0; j < D; ++j) o.c[j] = o.h[j] = 0.0;
+    return;
+  }
+#pragma unroll
+  for (int j = 0; j < D; ++j) {
+    o.c[j] = R.C[j * R.cap + q];
+    o.h[j] = R.H[j * R.cap + q];
+  }
+  o.lvl = R.L[q];
+  if (R.split) o.ax = R.PAX[q];
+}
+
+// The "+" or "-" half along axis ax.
+template <int D>
+__device__ __forceinline__ void halve(int ax, bool plus, double (&c)[D], double (&h)[D]) {
+#pragma unroll
+  for (int j = 0; j < D; ++j) {
+    if (j == ax) {
+      const double hp = h[j] * 0.5;
+      c[j] = plus ? c[j] + hp : c[j] - hp;
+      h[j] = hp;
+    }
+  }
+}
+
 template <int D, int L>
-__device__ __forceinline__ int load_active(const RegionSrc& R, int64_t r, int t, double (&c)[D],
-                                           double (&h)[D]) {
-  if (!R.pending) return load_region<D>(R, r, c, h);
+__device__ __forceinline__ int form_region(const RegionSrc& R, int64_t r, int t,
+                                           const Record<D>& o, double (&c)[D], double (&h)[D]) {
+#pragma unroll
+  for (int j = 0; j < D; ++j) {
+    c[j] = o.c[j];
+    h[j] = o.h[j];
+  }
+  int lvl = o.lvl;
+  if (R.split) {
+    halve<D>(o.ax, (R.pending ? o.e >> 8 : r) >= R.npar, c, h);
+    lvl += 1;
+  }
+  if (!R.pending) return lvl;
   const bool plus = r >= R.nkeep;
   const int64_t p = plus ? r - R.nkeep : r;
-  if (!GM_INB(p, R.cap / 2)) {
-#pragma unroll
-    for (int j = 0; j < D; ++j) c[j] = h[j] = 0.0;
-    return 0;
-  }
-  const int64_t e = R.IDX[p];
-  const int ax = (int)(e & 0xff);
-  const int lvl = load_region<D>(R, e >> 8, c, h);
+  if (!GM_INB(p, R.cap / 2)) return lvl;
+  const int ax = (int)(o.e & 0xff);
   if constexpr (L == 1) {
     double* const w = plus ? R.Hw : R.Cw;
 #pragma unroll
@@ -332,15 +386,16 @@ __device__ __forceinline__ int load_active(const RegionSrc& R, int64_t r, int t,
       R.Lw[p] = (uint16_t)lvl;
     }
   }
-#pragma unroll
-  for (int j = 0; j < D; ++j) {
-    if (j == ax) {
-      const double hp = h[j] * 0.5;
-      c[j] = plus ? c[j] + hp : c[j] - hp;
-      h[j] = hp;
-    }
-  }
+  halve<D>(ax, plus, c, h);
   return lvl + 1;
+}
+
+template <int D, int L>
+__device__ __forceinline__ int load_active(const RegionSrc& R, int64_t r, int t, double (&c)[D],
+                                           double (&h)[D]) {
+  Record<D> o;
+  load_record<D>(R, r, list_entry(R, r), o);
+  return form_region<D, L>(R, r, t, o, c, h);
 }
 
 // Level of region r of the active set.

@@ -75,7 +75,7 @@ RuleKernelFn gk_kernel(int d, int fam, bool batch);
 // Nodes of the rule the options select.
 int64_t nodes_per_region(int d);
 bool mapping_allowed(int d, int log2l);
-int rule_grid(int log2l, int64_t n, int d);
+int rule_grid(int log2l, int64_t n, int d, int kfam);
 // fixed_base: when not null, the run's device buffers are laid out from it
 // (the no-allocation entry point's fixed scratch, already checked to be large
 // enough) and the run allocates nothing: no workspace, no pinned status copy
