@@ -829,7 +829,10 @@ int run_batch(int n, const int* fam, const double* params, const int* d, const d
       rper[g] = 1;
     } else {
       const Tile t = tile_for(gd[g], base_family(gfam[g]));
-      rfn[g] = rule_kernel(gd[g], gfam[g], t.log2l, true);
+      // (the factored kernels of a batch's dimensions have one lane per region: an
+      // entry that asks for more gets the chain form's)
+      if (t.log2l >= 0) ra.P.fam = base_family(gfam[g]);
+      rfn[g] = rule_kernel(gd[g], ra.P.fam, t.log2l, true);
       rgrid[g] = t.grid > 0 ? t.grid : 2048;
       rper[g] = kRuleBlockSize >> std::max(0, t.log2l);
     }

@@ -55,3 +55,21 @@ def test_capacity_runs_out(small_partition):
     print("case capacity", flush=True)
     I, E, st = _batch(items, 300 * 32)
     assert np.all(np.asarray(st) == gm.MAX_REGIONS) and np.all(np.isfinite(E)) and np.all(np.isfinite(I))
+
+
+@pytest.mark.parametrize("fam", [1, 2, 4, 5, 6])
+@pytest.mark.parametrize("d,lanes", [(8, 4), (8, 16), (9, 16), (10, 4), (10, 64)])
+def test_tiles_of_several_lanes(fam, d, lanes):
+    """A tile entry with several lanes per region, where the one-lane kernel of the
+    dimension is the factored one: same statuses, and I to 1e-12 (the batch's bar)."""
+    args = ([fam] * 3, [W.family_params(fam, d, seed=50 * fam + k, difficulty=2.0) for k in range(3)],
+            [d] * 3, [np.zeros(d)] * 3, [np.ones(d)] * 3, [1e-3] * 3, [1e-300] * 3, 1 << 20)
+    print(f"case tile fam={fam} d={d} lanes={lanes}", flush=True)
+    _, i0, e0, s0 = gm.integrate_batch(*args)
+    gm.set_tile(d, fam, lanes, 0)
+    try:
+        _, i1, e1, s1 = gm.integrate_batch(*args)
+    finally:
+        gm.set_tile(d, fam, 0, 0)
+    assert np.array_equal(s0, s1)
+    assert np.all(np.abs(i1 - i0) <= 1e-12 * np.abs(i0))
