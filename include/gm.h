@@ -180,13 +180,16 @@ size_t gm_workspace_bytes(int d, int64_t max_regions, int mode);
  * gm_set_option -- process-wide knobs.  Returns GM_OK or GM_EINVAL.
  *   "init_log2_regions"  L0, initial partition 2^(d*floor(L0/d)) cells (default 12, 0..30)
  *   "max_iters"          iteration budget (default 10000, >= 1)
- *   "graph_iters"        iterations enqueued per host read of the device status
- *                        block.  gm_integrate: 0 (default) = automatic, 6 while
- *                        the active set is below 2^16 regions, 3 below 2^20, 2
- *                        above; k >= 1 = k iterations (at most 8); kernels are
- *                        launched directly (no graph) and those queued past the
- *                        end return at once.  gm_integrate_grad reads the status
- *                        after every iteration whatever the value.
+ *   "graph_iters"        iterations in flight.  gm_integrate: 0 (default) = two:
+ *                        the host reads each iteration's status from a pinned
+ *                        slot that the GPU writes and launches the next one
+ *                        meanwhile (with "timing", and in gm_integrate_noalloc
+ *                        where no slots were made before, 6 while the active
+ *                        set is below 2^16 regions, 3 below 2^20, 2 above,
+ *                        behind a copy of the status); k >= 1 = k iterations
+ *                        (at most 8); those launched past the end return at
+ *                        once.  gm_integrate_grad keeps one in flight whatever
+ *                        the value.
  *                        gm_integrate_batch: k >= 1 = one iteration's kernels
  *                        are captured k times into a hipGraph (kernel nodes
  *                        only) that is replayed until every item has stopped;

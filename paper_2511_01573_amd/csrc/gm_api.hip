@@ -1101,9 +1101,9 @@ static int forced_log2l() {
 // Lanes a launch should occupy before it takes fewer lanes per region: the
 // whole GPU at two wavefronts per SIMD is 256 CUs x 4 SIMDs x 2 x 64 = 131072,
 // but a lane's whole region costs less than several lanes' shares with their
-// common work, so the one-lane kernel wins from fewer on.  Rule kernel at d = 8,
-// corner peak, us for 1 / 4 / 16 lanes: n = 8192: 22 / 19 / 19, 32768: 24 / 30 /
-// 40, 65536: 24 / 43 / 75; d = 10: n = 32768: 59 / 46 / 62, 65536: 69 / 82 / 112.
+// common work, so the one-lane kernel wins from fewer on.  Corner peak (quotient
+// form) at d = 8, us for 1 / 4 / 16 lanes: n = 8192: 19 / 18 / 19, 32768: 20 / 27 /
+// 45, 65536: 23 / 40 / 78; d = 10: n = 32768: 47 / 41 / 60, 65536: 56 / 70 / 106.
 // Factored, d = 13 product peak, 1 / 4 / 16 / 64 lanes: n = 1024: 38 / 29 / 30 /
 // 24, 4096: 42 / 28 / 23 / 37, 16384: 43 / 29 / 38 / 91, 65536: 46 / 77 / 132 /
 // 345; up to d = 10 one lane is the fastest at every n (d = 8 Gaussian, n = 256:
