@@ -44,6 +44,7 @@ constexpr int kTileThreads = 256;  // 4 regions per thread per tile
 constexpr int kMaxRuleGrid = 16384;
 constexpr int kPruneBins = 66;  // budget factors 2^1 .. 2^64, bin 65 = beyond
 constexpr int kMaxTileGrid = 8192;
+constexpr int64_t kHostListCoords = 32768;  // region lists up to this many coordinates (gm_eval_regions)
 // The one-workgroup bookkeeping kernel (step_kernel): its threads, and the
 // largest active set it takes.
 constexpr int kStepThreads = 1024;
@@ -1658,16 +1659,39 @@ int gm_eval_regions(int integrand_id, const double* params, int d, const double*
   ra.n_fixed = n;
   // The caller's arrays as they are into the second buffer (levels: where Q will
   // be), laid out by a kernel: the host neither transposes nor allocates (30011
-  // regions at d = 7: 390 -> 277 us a call).
-  double* const cin = (double*)(base + lay.C[1]);
-  double* const hin = (double*)(base + lay.H[1]);
+  // regions at d = 7: 390 -> 277 us a call).  A short list is laid out here: the two
+  // layout kernels cost 27 us, the host 0.7 ns a coordinate (3 regions at d = 9: 85
+  // / 114 us, 2193 at d = 13: 172 / 194).
+  const bool on_host = n <= kHostListCoords / d;
+  double* const cin = (double*)(base + (on_host ? lay.C[0] : lay.C[1]));
+  double* const hin = (double*)(base + (on_host ? lay.H[0] : lay.H[1]));
   int32_t* const lin = (int32_t*)(base + lay.Q);
-  GM_HIP(hipMemcpyAsync(cin, c, sizeof(double) * d * n, hipMemcpyHostToDevice, s));
-  GM_HIP(hipMemcpyAsync(hin, h, sizeof(double) * d * n, hipMemcpyHostToDevice, s));
-  GM_HIP(hipMemcpyAsync(lin, lvl, sizeof(int32_t) * n, hipMemcpyHostToDevice, s));
-  hipLaunchKernelGGL(list_in_kernel, dim3((unsigned)lg), dim3(256), 0, s, cin, hin, lin, d, n,
-                     ra.C[0], ra.H[0], ra.L[0]);
-  GM_HIP(hipGetLastError());
+  std::vector<double> cs, hs;
+  std::vector<uint16_t> ls;
+  std::vector<uint8_t> ax;
+  if (on_host) {
+    cs.resize((size_t)d * n);
+    hs.resize((size_t)d * n);
+    ls.resize((size_t)n);
+    ax.resize((size_t)n);
+    for (int64_t r = 0; r < n; ++r) {
+      for (int j = 0; j < d; ++j) {
+        cs[(size_t)j * n + r] = c[r * d + j];
+        hs[(size_t)j * n + r] = h[r * d + j];
+      }
+      ls[r] = (uint16_t)lvl[r];
+    }
+  }
+  GM_HIP(hipMemcpyAsync(cin, on_host ? cs.data() : c, sizeof(double) * d * n, hipMemcpyHostToDevice, s));
+  GM_HIP(hipMemcpyAsync(hin, on_host ? hs.data() : h, sizeof(double) * d * n, hipMemcpyHostToDevice, s));
+  if (on_host) {
+    GM_HIP(hipMemcpyAsync(ra.L[0], ls.data(), sizeof(uint16_t) * n, hipMemcpyHostToDevice, s));
+  } else {
+    GM_HIP(hipMemcpyAsync(lin, lvl, sizeof(int32_t) * n, hipMemcpyHostToDevice, s));
+    hipLaunchKernelGGL(list_in_kernel, dim3((unsigned)lg), dim3(256), 0, s, cin, hin, lin, d, n,
+                       ra.C[0], ra.H[0], ra.L[0]);
+    GM_HIP(hipGetLastError());
+  }
   const int map = choose_mapping(d, integrand_id, n, true);
   // In chain form for every family: a region's err is a difference that a
   // resolved region cancels down to rounding, and a list's values are returned
@@ -1675,12 +1699,16 @@ int gm_eval_regions(int integrand_id, const double* params, int d, const double*
   // 7% of the call: 18 of 277 us for 30011 regions at d = 7).
   GM_HIP(launch_rule(d, integrand_id, map, ra, rule_grid(map, n, d, integrand_id), s));
   int32_t* const aout = (int32_t*)hin;
-  hipLaunchKernelGGL(list_out_kernel, dim3((unsigned)lg), dim3(256), 0, s, ra.AXIS, n, aout);
-  GM_HIP(hipGetLastError());
+  if (!on_host) {
+    hipLaunchKernelGGL(list_out_kernel, dim3((unsigned)lg), dim3(256), 0, s, ra.AXIS, n, aout);
+    GM_HIP(hipGetLastError());
+  }
   GM_HIP(hipMemcpyAsync(out_q, ra.Q, sizeof(double) * n, hipMemcpyDeviceToHost, s));
   GM_HIP(hipMemcpyAsync(out_err, ra.ERR, sizeof(double) * n, hipMemcpyDeviceToHost, s));
-  GM_HIP(hipMemcpyAsync(out_axis, aout, sizeof(int32_t) * n, hipMemcpyDeviceToHost, s));
+  if (on_host) GM_HIP(hipMemcpyAsync(ax.data(), ra.AXIS, n, hipMemcpyDeviceToHost, s));
+  else GM_HIP(hipMemcpyAsync(out_axis, aout, sizeof(int32_t) * n, hipMemcpyDeviceToHost, s));
   GM_HIP(hipStreamSynchronize(s));
+  for (size_t r = 0; r < ax.size(); ++r) out_axis[r] = ax[r];
   rc = check_bounds(GM_OK);
   if (rc != GM_OK) return rc;
   return GM_OK;

@@ -144,7 +144,7 @@ void factor_tpr_kernel(RuleArgs A) {
       load_record<D>(R, r, e, cur);
       if (v + stride < end) e = list_entry(R, region_of(v + stride));
     }
-    const int lvl = form_region<D, 1>(R, r, 0, cur, c, h);
+    const int lvl = form_region<D>(R, r, cur, c, h);
     double volo;
     const DevParams& P = region_params<BATCH>(A, buf, r, volo);
     const double vol = ldexp(volo, -lvl);

@@ -75,16 +75,22 @@ void rule9_kernel(RuleArgs A) {
   R9Slot<D>& sl = slots[g];
   dd qs = {0.0, 0.0}, es = {0.0, 0.0};
   int nonfin = 0;
-  for (int64_t base = start + (int64_t)blockIdx.x * RPB; base < n;
-       base += (int64_t)gridDim.x * RPB) {
+  // (The next region's list entry is read while this one is evaluated: corner peak,
+  // d = 12, 56.4 -> 55.3 ms.)
+  const int64_t stride = (int64_t)gridDim.x * RPB;
+  int64_t next = start + (int64_t)blockIdx.x * RPB + g;
+  next = next < n ? list_entry(R, next) : 0;
+  for (int64_t base = start + (int64_t)blockIdx.x * RPB; base < n; base += stride) {
     const int64_t r = base + g;
+    const int64_t entry = next;
+    if (r + stride < n) next = list_entry(R, r + stride);
     const bool valid = r < n;
     double volo;
     const DevParams& P = region_params<BATCH>(A, buf, valid ? r : start, volo);
     double c[D], h[D];
     int lvl = 0;
     if (valid) {
-      lvl = load_active<D, L>(R, r, s, c, h);
+      lvl = load_listed<D, L>(R, r, entry, s, c, h);
     } else {
 #pragma unroll
       for (int j = 0; j < D; ++j) {

@@ -172,3 +172,22 @@ def test_corner_both_sides_of_the_line(a):
     ref = O.rule_many(3, p, act["c"][idx], act["h"][idx], act["lvl"][idx], 1.0)
     assert np.all(np.abs(act["Q"][idx] - ref["Q"]) <= 4e-13 * np.maximum(np.abs(ref["Q"]), ref["scaleQ"]))
     assert np.all(np.abs(act["err"][idx] - ref["err"]) <= 4e-13 * ref["scaleE"])
+
+
+@pytest.mark.parametrize("n", [8191, 8192, 8193])
+def test_list_layouts(n):
+    """Region lists on either side of the line (32768 coordinates) below which the
+    host lays them out: the bits of the same regions in short lists."""
+    d = 4
+    rng = np.random.default_rng(n)
+    p = W.family_params(4, d, seed=9)
+    lvl = rng.integers(0, 12, n).astype(np.int32)
+    h = np.repeat(np.ldexp(0.5, -(lvl // d))[:, None], d, axis=1)
+    c = h + rng.uniform(0.0, 1.0, (n, d)) * (1.0 - 2.0 * h)
+    lo, hi = W.unit_box(d)
+    print(f"case list n={n}", flush=True)
+    whole = gm.eval_regions(4, p, lo, hi, c, h, lvl)
+    for a in range(0, n, 3000):
+        part = gm.eval_regions(4, p, lo, hi, c[a:a + 3000], h[a:a + 3000], lvl[a:a + 3000])
+        for x, y in zip(whole, part):
+            assert np.array_equal(x[a:a + 3000], y)
