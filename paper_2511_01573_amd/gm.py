@@ -231,7 +231,7 @@ def integrate_batch(families, params_list, ds, los, his, rel_tols, abs_tols, max
                     stream=None):
     """gm_integrate_batch; returns (rc, est[n], err[n], status[n])."""
     n = len(families)
-    fam = np.ascontiguousarray([FAMILIES[f] if type(f) is str else int(f) for f in families],
+    fam = np.ascontiguousarray([FAMILIES[f] if isinstance(f, str) else int(f) for f in families],
                                dtype=np.intc)
     d = np.ascontiguousarray(ds, dtype=np.intc)
     params, lo, hi = _packed(params_list), _packed(los), _packed(his)
