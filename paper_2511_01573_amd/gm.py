@@ -221,10 +221,13 @@ def integrate_grad(family, params, lo, hi, rel_tol, abs_tol=1e-16, max_regions=1
 
 def _packed(items):
     """The items' values end to end as one float64 array."""
-    # arrays are joined first and converted once (4096 items: 0.9 ms against 1.6)
-    if not all(type(x) is np.ndarray for x in items):
+    # float64 arrays are joined as they are, anything else item by item first: joined
+    # before, items of mixed types would take a common type that can differ from what
+    # each is by itself (a string of a float32's digits) or refuse them
+    # (4096 float64 items: 0.9 ms against 1.6)
+    if set(map(type, items)) != {np.ndarray} or {x.dtype for x in items} != {np.dtype(float)}:
         items = [np.asarray(x, float) for x in items]
-    return np.ascontiguousarray(np.concatenate(items), dtype=np.float64)
+    return np.ascontiguousarray(np.concatenate(items))
 
 
 def integrate_batch(families, params_list, ds, los, his, rel_tols, abs_tols, max_regions_total,

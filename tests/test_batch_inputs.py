@@ -5,6 +5,8 @@ every argument."""
 from __future__ import annotations
 
 import enum
+import itertools
+import warnings
 
 import numpy as np
 import pytest
@@ -38,3 +40,30 @@ def test_unknown_family_name():
     p, lo, hi = np.ones(2 * d), np.zeros(d), np.ones(d)
     with pytest.raises(KeyError):
         gm.integrate_batch([np.str_("gauss")], [p], [d], [lo], [hi], [1e-3], [1e-16], 1 << 16)
+
+
+DTYPES = ["bool", "i1", "u1", "i2", "u2", "i4", "u4", "i8", "u8", "f2", "f4", "f8", "g", "c8",
+          "c16", "O", "U24"]
+
+
+@pytest.mark.parametrize("pair", list(itertools.combinations_with_replacement(DTYPES, 2)),
+                         ids=lambda p: "-".join(p))
+def test_packed_arrays_of_mixed_types(pair):
+    """Items of any two types are joined as the float64 values that each has by itself."""
+    base = np.array([1, 0, 1, 0, 1])
+    wide = np.array([2.0 ** 53 + 2, 0.1, 3.0, -7.25, 1e-9])
+    items = []
+    for k, t in enumerate(pair):
+        x = base if t == "bool" else (base + 100 + k) if t[0] in "iu" else wide.astype("f4") if t == "f2" else wide
+        if t in ("i8", "u8"):
+            x = base + (2 ** 53 + 3)
+        with warnings.catch_warnings():
+            warnings.simplefilter("ignore")
+            items.append(x.astype(t))
+    items.append([1.5, 2, 3])
+    for some in (items[:2], items, [items[1], items[0]]):
+        with warnings.catch_warnings():
+            warnings.simplefilter("ignore")
+            want = np.concatenate([np.asarray(x, float) for x in some])
+            got = gm._packed(some)
+        assert got.dtype == np.float64 and np.array_equal(got, want, equal_nan=True)
