@@ -221,6 +221,7 @@ def integrate_grad(family, params, lo, hi, rel_tol, abs_tol=1e-16, max_regions=1
 
 def _packed(items):
     """The items' values end to end as one float64 array."""
+    items = list(items)  # (may be an iterator)
     # float64 arrays are joined as they are, anything else item by item first: joined
     # before, items of mixed types would take a common type that can differ from what
     # each is by itself (a string of a float32's digits) or refuse them

@@ -67,3 +67,11 @@ def test_packed_arrays_of_mixed_types(pair):
             want = np.concatenate([np.asarray(x, float) for x in some])
             got = gm._packed(some)
         assert got.dtype == np.float64 and np.array_equal(got, want, equal_nan=True)
+
+
+@pytest.mark.parametrize("item", [list, np.array], ids=["lists", "arrays"])
+def test_packed_takes_iterators(item):
+    """Every item of an iterator arrives, whatever its items are."""
+    rows = [[1.0, 2.0, 3.0], [4.0, 5.0, 6.0], [7.0, 8.0, 9.0]]
+    got = gm._packed(item(r) for r in rows)
+    assert np.array_equal(got, np.arange(1.0, 10.0))
