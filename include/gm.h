@@ -183,11 +183,14 @@ size_t gm_workspace_bytes(int d, int64_t max_regions, int mode);
  *   "graph_iters"        iterations in flight.  gm_integrate: 0 (default) = two:
  *                        the host reads each iteration's status from a pinned
  *                        slot that the GPU writes and launches the next one
- *                        meanwhile (with "timing", and in gm_integrate_noalloc
- *                        where no slots were made before, 6 while the active
- *                        set is below 2^16 regions, 3 below 2^20, 2 above,
- *                        behind a copy of the status); k >= 1 = k iterations
- *                        (at most 8); those launched past the end return at
+ *                        meanwhile (gm_integrate_noalloc where no slots were
+ *                        made before: up to 6 while the active set is below
+ *                        2^16 regions, 3 below 2^20, 2 above, behind a copy of
+ *                        the status); k >= 1 = up to k iterations (at most 8).
+ *                        The number changes no result (k = 1 sizes a launch by
+ *                        the count itself instead of twice the one before, which
+ *                        can change the kernels' mapping and with it last bits);
+ *                        iterations launched past the end return at
  *                        once.  gm_integrate_grad keeps one in flight whatever
  *                        the value.
  *                        gm_integrate_batch: k >= 1 = one iteration's kernels

@@ -1422,9 +1422,16 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
   // and keeps `ahead` iterations in flight: two, so that the GPU never waits for
   // the host (an iteration takes 15 us or more, a read and its launches 5), and
   // at most one is launched in vain.  Gradient mode keeps one (the leaf store
-  // grows on the host's side).  Without slots (events to read, or none made on
-  // the no-allocation path) the host launches a few iterations and copies the
-  // status behind them: 6 below 2^16 active regions, 3 below 2^20, 2 above.
+  // grows on the host's side).  Without slots (none made before a call on the
+  // no-allocation path) the host launches a few iterations and copies the status
+  // behind them: 6 below 2^16 active regions, 3 below 2^20, 2 above.
+  //
+  // How many are in flight decides neither the kernels nor a bit of the result:
+  // with more than one, iteration k takes the rule-kernel mapping of twice
+  // iteration k - 1's count (what is known of it with two in flight), and is not
+  // launched before that count is known unless every count it could have gives
+  // the same mapping.  (The grid only bounds the workgroups: a region's
+  // workgroup, and with it the order of the sums, is the same in every grid.)
   hipEvent_t ev[kMaxAhead][5] = {};
   // (events are created per run: not on the no-allocation path)
   const bool timing = g_opt.timing != 0 && !fixed_base;  // rule kernel only
@@ -1432,10 +1439,11 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
   if (timing)
     for (auto& row : ev)
       for (auto& e : row) GM_HIP(hipEventCreate(&e));
-  StatusSlot* const slots = timing ? nullptr : status_slots(fixed_base == nullptr);
+  StatusSlot* const slots = status_slots(fixed_base == nullptr);
 
   const ListFn list_fn = keep_leaves ? leaf_list_fn(d, true) : list_kernel<0, true>;
   int64_t n = n0;             // active regions of iteration `seen`
+  int64_t n_before = 0;       // ... and of the one before it
   int64_t leaves_have = 0;
   int64_t seen = 0, launched = 0;  // iterations whose status is known / launched
   const int64_t seq0 = g_status_seq;
@@ -1457,7 +1465,13 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
     int64_t nb = n;
     for (int64_t k = seen; k < launched; ++k) nb = std::min<int64_t>(cap, 2 * nb);
     for (; launched < seen + ahead; ++launched) {
-      const int map = choose_mapping(d, kfam, nb, false);
+      int64_t nm = nb;  // the count the mapping goes by
+      if (ahead > 1 && launched > 0) {
+        const int64_t k = launched - seen;
+        if (k < 2) nm = std::min<int64_t>(cap, 2 * (k == 0 ? n_before : n));
+        else if (choose_mapping(d, kfam, nb, false) != choose_mapping(d, kfam, 2, false)) break;
+      }
+      const int map = choose_mapping(d, kfam, nm, false);
       const int rg = rule_grid(map, nb, d, kfam);
       const int tg = tile_grid_for(nb);
       g_stats.lanes_per_region = lanes_of_mapping(map, d);
@@ -1518,6 +1532,7 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
       for (int64_t k = before; k < seen; ++k) {
         hipEvent_t* const e = ev[k % kMaxAhead];
         float t[4] = {0, 0, 0, 0};
+        GM_HIP(hipEventSynchronize(e[phases ? 4 : 1]));  // (the slot is filled before it)
         for (int q = 0; q < (phases ? 4 : 1); ++q) GM_HIP(hipEventElapsedTime(&t[q], e[q], e[q + 1]));
         g_stats.rule_ms += t[0];
         g_stats.reduce_ms += t[1];
@@ -1533,6 +1548,7 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
     leaves_have = hst.leaf_count;
     if (hst.done) break;
     n = hst.n_active;
+    n_before = hst.n_prev;
   }
   // (an iteration launched in vain returns at once, but is part of this call)
   if (slots) GM_HIP(hipStreamSynchronize(s));
