@@ -1309,6 +1309,16 @@ static int noalloc_scratch(char** out) {
   return GM_OK;
 }
 
+// A run's timing events.
+struct RunEvents {
+  hipEvent_t ev[kMaxAhead][5] = {};
+  ~RunEvents() {
+    for (auto& row : ev)
+      for (auto& e : row)
+        if (e) (void)hipEventDestroy(e);
+  }
+};
+
 // One adaptive run on the device (gm_integrate and the forward pass of
 // gm_integrate_grad).  On return the status block holds the final state.
 int run_adaptive(int fam, const double* params, int d, const double* lo, const double* hi,
@@ -1409,6 +1419,8 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
   hst.prune_on = g_opt.prune;
   ia.st = st;
   ia.status = hst;
+  RunEvents events;
+  DrainOnError drain{s};
   {
     int g = (int)std::min<int64_t>((n0 + 255) / 256, 4096);
     hipLaunchKernelGGL(init_kernel, dim3(g), dim3(256), 0, s, ia);
@@ -1432,12 +1444,11 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
   // launched before that count is known unless every count it could have gives
   // the same mapping.  (The grid only bounds the workgroups: a region's
   // workgroup, and with it the order of the sums, is the same in every grid.)
-  hipEvent_t ev[kMaxAhead][5] = {};
   // (events are created per run: not on the no-allocation path)
   const bool timing = g_opt.timing != 0 && !fixed_base;  // rule kernel only
   const bool phases = timing && g_opt.timing >= 2;       // every phase
   if (timing)
-    for (auto& row : ev)
+    for (auto& row : events.ev)
       for (auto& e : row) GM_HIP(hipEventCreate(&e));
   StatusSlot* const slots = status_slots(fixed_base == nullptr);
 
@@ -1475,8 +1486,9 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
       const int rg = rule_grid(map, nb, d, kfam);
       const int tg = tile_grid_for(nb);
       g_stats.lanes_per_region = lanes_of_mapping(map, d);
-      hipEvent_t* const e = ev[launched % kMaxAhead];
-      const Mirror mir{slots ? slots + launched % kSlots : nullptr, ++g_status_seq};
+      hipEvent_t* const e = events.ev[launched % kMaxAhead];
+      const int64_t seq = ++g_status_seq;
+      const Mirror mir{slots ? slots + seq % kSlots : nullptr, seq};
       if (timing) GM_HIP(hipEventRecord(e[0], s));
       GM_HIP(launch_rule(d, kfam, map, ra, rg, s));
       if (timing) GM_HIP(hipEventRecord(e[1], s));
@@ -1515,7 +1527,8 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
     }
     const int64_t before = seen;
     if (slots) {
-      rc = await_slot(slots + seen % kSlots, seq0 + seen + 1, s, &hst);
+      const int64_t seq = seq0 + seen + 1;
+      rc = await_slot(slots + seq % kSlots, seq, s, &hst);
       if (rc != GM_OK) return rc;
       seen += 1;
     } else {
@@ -1530,7 +1543,7 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
     }
     if (timing) {
       for (int64_t k = before; k < seen; ++k) {
-        hipEvent_t* const e = ev[k % kMaxAhead];
+        hipEvent_t* const e = events.ev[k % kMaxAhead];
         float t[4] = {0, 0, 0, 0};
         GM_HIP(hipEventSynchronize(e[phases ? 4 : 1]));  // (the slot is filled before it)
         for (int q = 0; q < (phases ? 4 : 1); ++q) GM_HIP(hipEventElapsedTime(&t[q], e[q], e[q + 1]));
@@ -1551,10 +1564,8 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
     n_before = hst.n_prev;
   }
   // (an iteration launched in vain returns at once, but is part of this call)
+  drain.owed = false;
   if (slots) GM_HIP(hipStreamSynchronize(s));
-  if (timing)
-    for (auto& row : ev)
-      for (auto& e : row) (void)hipEventDestroy(e);
 
   out->I = hst.I;
   out->E = hst.E;
@@ -1685,6 +1696,7 @@ int gm_eval_regions(int integrand_id, const double* params, int d, const double*
   std::vector<double> cs, hs;
   std::vector<uint16_t> ls;
   std::vector<uint8_t> ax;
+  DrainOnError drain{s};
   if (on_host) {
     cs.resize((size_t)d * n);
     hs.resize((size_t)d * n);
@@ -1724,6 +1736,7 @@ int gm_eval_regions(int integrand_id, const double* params, int d, const double*
   if (on_host) GM_HIP(hipMemcpyAsync(ax.data(), ra.AXIS, n, hipMemcpyDeviceToHost, s));
   else GM_HIP(hipMemcpyAsync(out_axis, aout, sizeof(int32_t) * n, hipMemcpyDeviceToHost, s));
   GM_HIP(hipStreamSynchronize(s));
+  drain.owed = false;
   for (size_t r = 0; r < ax.size(); ++r) out_axis[r] = ax[r];
   rc = check_bounds(GM_OK);
   if (rc != GM_OK) return rc;

@@ -149,6 +149,7 @@ extern "C" int gm_integrate_grad(int integrand_id, const double* params, int d, 
     active.cap = rr.cap;
     active.npar = rr.final_npar;
     active.split = rr.final_split;
+    DrainOnError drain{s};
     int64_t blk = 0;
     for (int pt = 0; pt < nparts; ++pt) {
       const AdjFn fn = factored ? factored : adj_fn(d, integrand_id, r9, parts[pt]);
@@ -166,6 +167,7 @@ extern "C" int gm_integrate_grad(int integrand_id, const double* params, int d, 
     if (e == hipSuccess) e = hipMemcpyAsync(grad.data(), dout, sizeof(double) * 2 * d, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return record_hip_error(e);
+    drain.owed = false;
     rc = check_bounds(GM_OK);
     if (rc != GM_OK) return rc;
   }

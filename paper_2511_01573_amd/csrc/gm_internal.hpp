@@ -76,6 +76,20 @@ RuleKernelFn gk_kernel(int d, int fam, bool batch);
 int64_t nodes_per_region(int d);
 bool mapping_allowed(int d, int log2l);
 int rule_grid(int log2l, int64_t n, int d, int kfam);
+
+// The wait that a call owes its caller when it returns early with work enqueued:
+// a status is read while the iteration's last kernel may still run, and the
+// workspace, the leaf store and the status slots are the next call's.
+struct DrainOnError {
+  hipStream_t s;
+  bool owed = true;
+  ~DrainOnError() {
+    if (!owed) return;
+    (void)hipStreamSynchronize(s);
+    (void)hipGetLastError();
+  }
+};
+
 // fixed_base: when not null, the run's device buffers are laid out from it
 // (the no-allocation entry point's fixed scratch, already checked to be large
 // enough) and the run allocates nothing: no workspace, no pinned status copy
