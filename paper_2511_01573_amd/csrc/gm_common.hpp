@@ -236,7 +236,7 @@ __device__ __forceinline__ int64_t wave_sum_i64(int64_t v) {
 // The split does not move regions: it lists the kept ones (IDX[p] = region << 8
 // | split axis, p < n_keep), and the rule kernel of the next iteration forms
 // record p from that region's own record, writes it to the other buffer and
-// evaluates its children (load_active).  A record is so read and written once
+// evaluates its children (form_region, load_axes).  A record is so read and written once
 // per iteration, inside the kernel that is bound by arithmetic, instead of read
 // and written by a kernel of its own and read again (d = 8 Gaussian at 1e-7: the
 // scatter took 0.6 of 3.8 ms).  The list lies in the unused upper half of the
@@ -376,49 +376,80 @@ __device__ __forceinline__ int form_region(const RegionSrc& R, int64_t r, const 
   return lvl + 1;
 }
 
-// The same in one step, from the kept list's entry e of the region; several lanes
-// per region (L threads work on it, this one is number t) share the writing.
-// (Through Record the compiler put an array of the multi-lane kernels in scratch
-// memory: degree 9, d = 12, corner peak, 52.6 -> 61.4 ms.)
-template <int D, int L>
-__device__ __forceinline__ int load_listed(const RegionSrc& R, int64_t r, int64_t e, int t,
-                                           double (&c)[D], double (&h)[D]) {
-  if constexpr (L == 1) {
-    Record<D> o;
-    load_record<D>(R, r, e, o);
-    return form_region<D>(R, r, o, c, h);
-  }
-  if (!R.pending) return load_region<D>(R, r, c, h);
-  const bool plus = r >= R.nkeep;
+// The same in one step.
+template <int D>
+__device__ __forceinline__ int load_active(const RegionSrc& R, int64_t r, double (&c)[D],
+                                           double (&h)[D]) {
+  Record<D> o;
+  load_record<D>(R, r, list_entry(R, r), o);
+  return form_region<D>(R, r, o, c, h);
+}
+
+// Region r (kept list entry e) for L threads that work on it, this one number t:
+// the axes are dealt out, and each(j, c_j, h_j) gets the thread's own; where there
+// is no region (!valid) a harmless one.  A thread so reads, halves and writes D / L
+// coordinates, and what all need goes through LDS.  (Holding every axis in every
+// lane cost 4 D registers through the whole kernel, and writing a share of them made
+// the lane number an index into them, which the compiler resolved with an array in
+// scratch memory in the kernels with L >= D, 48 to 144 B a lane; and each axis' terms
+// were formed by one lane after another.  Degree-9 runs, ms: corner peak d = 12 33.2
+// -> 23.5 (203 -> 146 registers), C0 d = 11 64.0 -> 23.6, product peak d = 13 18.9 ->
+// 7.9; degree 7, 35 regions in 6 iterations at d = 13: 244 -> 157 us.)
+template <int D, int L, class Each>
+__device__ __forceinline__ int load_axes(const RegionSrc& R, bool valid, int64_t r, int64_t e,
+                                         int t, Each each) {
+  const bool plus = R.pending && r >= R.nkeep;
   const int64_t p = plus ? r - R.nkeep : r;
-  if (!GM_INB(p, R.cap / 2)) {
-#pragma unroll
-    for (int j = 0; j < D; ++j) c[j] = h[j] = 0.0;
-    return 0;
+  const int64_t a = R.pending ? e >> 8 : r;
+  const bool up = R.split && a >= R.npar;
+  const int64_t q = up ? a - R.npar : a;
+  const bool ok = valid && GM_INB(q, R.cap) && (!R.pending || GM_INB(p, R.cap / 2));
+  const int ax = R.pending ? (int)(e & 0xff) : -1;
+  int lvl = 0, old = -1;
+  if (ok) {
+    lvl = R.L[q];
+    if (R.split) {
+      old = R.PAX[q];
+      lvl += 1;
+    }
   }
-  const int ax = (int)(e & 0xff);
-  const int lvl = load_region<D>(R, e >> 8, c, h);
-  if (!plus) {
 #pragma unroll
-    for (int j = 0; j < D; ++j) {
-      if ((j & (L - 1)) == t) {
-        R.Cw[j * R.cap + p] = c[j];
-        R.Hw[j * R.cap + p] = h[j];
+  for (int j0 = 0; j0 < D; j0 += L) {
+    const int j = j0 + t;
+    if (j >= D) break;
+    double c = 0.5, h = 0.25;
+    if (ok) {
+      c = R.C[j * R.cap + q];
+      h = R.H[j * R.cap + q];
+      if (j == old) {
+        h *= 0.5;
+        c = up ? c + h : c - h;
+      }
+      if (R.pending && !plus) {
+        R.Cw[j * R.cap + p] = c;
+        R.Hw[j * R.cap + p] = h;
+      }
+      if (j == ax) {
+        h *= 0.5;
+        c = plus ? c + h : c - h;
       }
     }
-    if (t == 0) {
+    each(j, c, h);
+  }
+  if (ok && R.pending) {
+    if (!plus && t == 0) {
       R.PAXw[p] = (uint8_t)ax;
       R.Lw[p] = (uint16_t)lvl;
     }
+    lvl += 1;
   }
-  halve<D>(ax, plus, c, h);
-  return lvl + 1;
+  return lvl;
 }
 
-template <int D, int L>
-__device__ __forceinline__ int load_active(const RegionSrc& R, int64_t r, int t, double (&c)[D],
-                                           double (&h)[D]) {
-  return load_listed<D, L>(R, r, list_entry(R, r), t, c, h);
+// Between lanes of one wavefront: what they wrote to LDS before is read after.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
 // Level of region r of the active set.

@@ -161,15 +161,34 @@ void factor_tpr_kernel(RuleArgs A) {
 // WPR: L = 2^LOG2L lanes per region (d > 10).
 // ---------------------------------------------------------------------------
 // LDS per region: the factors of every axis at +-l2, +-l3, +-l5 and the centre,
-// the products of the centre factors before and after each axis, and the
-// fourth differences.
+// the products of the centre factors before and after each axis, and the region
+// itself.  An axis' fourth difference and its scale take the place of its +-l2
+// factors, which its axis nodes alone read (with four lanes a region the slots
+// decide how many workgroups a CU holds).
 template <int D, int FAM>
 struct FactorSlot {
   using T = typename Alg<FAM>::T;
   static constexpr bool U = Alg<FAM>::kUnitCentre;
   T t2[2][D], t3[2][D], t5[2][D];
   T tc[U ? 1 : D], pre[U ? 1 : D], suf[U ? 1 : D];
-  double dv[D], sc[D];
+  double c[D], h[D];
+
+  __device__ __forceinline__ void put_diff(int i, double dv, double sc) {
+    if constexpr (U) {
+      t2[0][i] = T{dv, sc};
+    } else {
+      t2[0][i] = dv;
+      t2[1][i] = sc;
+    }
+  }
+  __device__ __forceinline__ double dv(int i) const {
+    if constexpr (U) return t2[0][i].r;
+    else return t2[0][i];
+  }
+  __device__ __forceinline__ double sc(int i) const {
+    if constexpr (U) return t2[0][i].i;
+    else return t2[1][i];
+  }
 };
 
 template <int D, int FAM, int LOG2L>
@@ -196,33 +215,18 @@ __global__ __launch_bounds__(kRuleBlock) void factor_wpr_kernel(RuleArgs A) {
     const bool valid = r < n;
     double volo;
     const DevParams& P = region_params<false>(A, buf, valid ? r : start, volo);
-    double c[D], h[D];
-    int lvl = 0;
-    if (valid) {
-      lvl = load_active<D, L>(R, r, s, c, h);
-    } else {
-#pragma unroll
-      for (int j = 0; j < D; ++j) {
-        c[j] = 0.5;
-        h[j] = 0.25;
-      }
-    }
     // The region's factors, the axes dealt out to the lanes.
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-      if ((j & (L - 1)) == s) {
-        F::pair(P, j, c[j], h[j], K.lam2, sl.t2[0][j], sl.t2[1][j]);
-        F::pair(P, j, c[j], h[j], K.lam3, sl.t3[0][j], sl.t3[1][j]);
-        F::pair(P, j, c[j], h[j], K.lam5, sl.t5[0][j], sl.t5[1][j]);
-        if constexpr (!U) {
-          const double x[1] = {c[j]};
-          T t[1];
-          F::template terms<1>(P, j, x, t);
-          sl.tc[j] = t[0];
-        }
-      }
-    }
-    const T base = F::template base<D>(P, c);
+    const int lvl = load_axes<D, L>(R, valid, r, valid ? list_entry(R, r) : 0, s,
+                                    [&](int j, double c, double h) {
+                                      sl.c[j] = c;
+                                      sl.h[j] = h;
+                                      F::pair(P, j, c, h, K.lam2, sl.t2[0][j], sl.t2[1][j]);
+                                      F::pair(P, j, c, h, K.lam3, sl.t3[0][j], sl.t3[1][j]);
+                                      F::pair(P, j, c, h, K.lam5, sl.t5[0][j], sl.t5[1][j]);
+                                      F::centre(P, j, c, sl.tc);
+                                    });
+    wave_lds_sync();
+    const T base = F::template base<D>(P, sl.c);
     __syncthreads();
     T tc[U ? 1 : D];
     T full = base;
@@ -262,8 +266,7 @@ __global__ __launch_bounds__(kRuleBlock) void factor_wpr_kernel(RuleArgs A) {
       ks_add(S3, f[2] + f[3]);
       double dv, scv;
       fourth_diff(K, f0, f[0], f[1], f[2], f[3], dv, scv);
-      sl.dv[i] = dv;
-      sl.sc[i] = scv;
+      sl.put_diff(i, dv, scv);
     }
     // Class 4, one axis pair per item: the centre factors between the two axes
     // are multiplied from the lane's registers with the item's bounds as
@@ -313,11 +316,11 @@ __global__ __launch_bounds__(kRuleBlock) void factor_wpr_kernel(RuleArgs A) {
       double dv[D], scale = 0.0;
 #pragma unroll
       for (int i = 0; i < D; ++i) {
-        dv[i] = sl.dv[i];
-        scale = sl.sc[i] > scale ? sl.sc[i] : scale;
+        dv[i] = sl.dv(i);
+        scale = sl.sc(i) > scale ? sl.sc(i) : scale;
       }
-      split_axis<D>(K, dv, scale, c, h, o);
-      o.nonfinite |= !Fam<base_family(FAM)>::in_range(P, c, h);
+      split_axis<D>(K, dv, scale, sl.c, sl.h, o);
+      o.nonfinite |= !Fam<base_family(FAM)>::in_range(P, sl.c, sl.h);
       store_result(A, r, o);
       dd_add(qs, o.q);
       dd_add(es, o.err);

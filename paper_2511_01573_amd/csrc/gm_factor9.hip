@@ -29,12 +29,12 @@ struct Factor9Slot {
   T tp[6][D];
   T tc[U ? 1 : D], pre[U ? 1 : D], suf[U ? 1 : D];
   T mid[U ? 1 : D * (D - 1) / 2];  // strictly between axes i < j: [j (j - 1) / 2 + i]
-  double dv[D], sc[D];
+  double c[D], h[D], dv[D], sc[D];
 };
 
-// Three wavefronts per SIMD up to d = 10 (at most a few values spill to
-// scratch, and the extra wavefront hides more latency); two above, where the
-// spill would grow.
+// Three wavefronts per SIMD at d = 10 (the rotation family spills 16 registers
+// there); two above, where the compiler uses 128 to 200 registers (rotations: 200 to
+// 256, with up to 18 spilled from d = 14 on).
 template <int D, int FAM, int LOG2L>
 __global__ __launch_bounds__(kRuleBlock) __attribute__((amdgpu_waves_per_eu(D <= 10 ? 3 : 2)))
 void factor9_kernel(RuleArgs A) {
@@ -62,32 +62,17 @@ void factor9_kernel(RuleArgs A) {
     const bool valid = r < n;
     double volo;
     const DevParams& P = region_params<false>(A, buf, valid ? r : start, volo);
-    double c[D], h[D];
-    int lvl = 0;
-    if (valid) {
-      lvl = load_active<D, L>(R, r, s, c, h);
-    } else {
-#pragma unroll
-      for (int j = 0; j < D; ++j) {
-        c[j] = 0.5;
-        h[j] = 0.25;
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-      if ((j & (L - 1)) == s) {
-        F::pair(P, j, c[j], h[j], K.lam2, sl.tp[0][j], sl.tp[1][j]);
-        F::pair(P, j, c[j], h[j], K.lam3, sl.tp[2][j], sl.tp[3][j]);
-        F::pair(P, j, c[j], h[j], K.lam6, sl.tp[4][j], sl.tp[5][j]);
-        if constexpr (!U) {
-          const double x[1] = {c[j]};
-          T t[1];
-          F::template terms<1>(P, j, x, t);
-          sl.tc[j] = t[0];
-        }
-      }
-    }
-    const T base = F::template base<D>(P, c);
+    const int lvl = load_axes<D, L>(R, valid, r, valid ? list_entry(R, r) : 0, s,
+                                    [&](int j, double c, double h) {
+                                      sl.c[j] = c;
+                                      sl.h[j] = h;
+                                      F::pair(P, j, c, h, K.lam2, sl.tp[0][j], sl.tp[1][j]);
+                                      F::pair(P, j, c, h, K.lam3, sl.tp[2][j], sl.tp[3][j]);
+                                      F::pair(P, j, c, h, K.lam6, sl.tp[4][j], sl.tp[5][j]);
+                                      F::centre(P, j, c, sl.tc);
+                                    });
+    wave_lds_sync();
+    const T base = F::template base<D>(P, sl.c);
     __syncthreads();
     T full = base;
     if constexpr (!U) {
@@ -129,10 +114,7 @@ void factor9_kernel(RuleArgs A) {
     }
     // the corner terms take the l6 terms' place (each lane the axes it alone
     // read there)
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-      if ((j & (L - 1)) == s) F::pair(P, j, c[j], h[j], K.lam5, sl.tp[4][j], sl.tp[5][j]);
-    }
+    for (int j = s; j < D; j += L) F::pair(P, j, sl.c[j], sl.h[j], K.lam5, sl.tp[4][j], sl.tp[5][j]);
     // Axis pairs i < j: class 4 (+-l4, +-l4) and class 7 in both orders.
     for (int it = s; it < NPAIR; it += L) {
       const int pk = kItems<D>.pair[it];
@@ -198,8 +180,8 @@ void factor9_kernel(RuleArgs A) {
         dv[i] = sl.dv[i];
         scale = sl.sc[i] > scale ? sl.sc[i] : scale;
       }
-      split_axis<D>(K, dv, scale, c, h, o);
-      o.nonfinite |= !Fam<base_family(FAM)>::in_range(P, c, h);
+      split_axis<D>(K, dv, scale, sl.c, sl.h, o);
+      o.nonfinite |= !Fam<base_family(FAM)>::in_range(P, sl.c, sl.h);
       store_result(A, r, o);
       dd_add(qs, o.q);
       dd_add(es, o.err);
@@ -350,7 +332,7 @@ void factor9_tpr_kernel(RuleArgs A) {
   for (; v < end; v += stride) {
     const int64_t r = pairs ? ((v & 1) ? R.nkeep + (v >> 1) : (v >> 1)) : v;
     double c[D], h[D];
-    const int lvl = load_active<D, 1>(R, r, 0, c, h);
+    const int lvl = load_active<D>(R, r, c, h);
     const RegionResult o = factor9_region<D, FAM>(A.P, A.K, c, h, ldexp(A.vol_omega, -lvl));
     store_result(A, r, o);
     dd_add(qs, o.q);

@@ -102,6 +102,7 @@ __global__ __launch_bounds__(kRuleBlock) void rule_gk_kernel(RuleArgs A) {
   const int slot = threadIdx.x / NT, t = threadIdx.x % NT;
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
   __shared__ double tt[RPB][D][15];
+  __shared__ double cs[RPB][D], hs[RPB][D];
   __shared__ dd red[kRuleBlock / 64][3 + D];  // per-wavefront partial sums
   dd qs = {0.0, 0.0}, es = {0.0, 0.0};
   int nonfin = 0;
@@ -112,21 +113,17 @@ __global__ __launch_bounds__(kRuleBlock) void rule_gk_kernel(RuleArgs A) {
     const bool ok = r < end;
     double volo;
     const DevParams& P = region_params<BATCH>(A, buf, ok ? r : start, volo);
-    double c[D], h[D];
-    int lvl = 0;
-    if (ok) {
-      lvl = load_active<D, NT>(R, r, t, c, h);
-    } else {
-#pragma unroll
-      for (int j = 0; j < D; ++j) {
-        c[j] = 0.0;
-        h[j] = 0.0;
-      }
-    }
-    if (ok && t < 15) {
-      const double xk = gk::kX[t];
-#pragma unroll
-      for (int j = 0; j < D; ++j) tt[slot][j][t] = F::term(P, j, fma(xk, h[j], c[j]));
+    double* const c = cs[slot];
+    double* const h = hs[slot];
+    const int lvl = load_axes<D, NT>(R, ok, r, ok ? list_entry(R, r) : 0, t,
+                                     [&](int j, double cj, double hj) {
+                                       c[j] = cj;
+                                       h[j] = hj;
+                                     });
+    __syncthreads();
+    for (int o = t; o < 15 * D; o += NT) {
+      const int j = o / 15, k = o - 15 * j;
+      tt[slot][j][k] = F::term(P, j, fma(gk::kX[k], h[j], c[j]));
     }
     __syncthreads();
     double sa = 0.0, sb = 0.0, sab = 0.0, sm[D];
@@ -231,7 +228,7 @@ __global__ __launch_bounds__(kRuleBlock) void rule_gk_kernel(RuleArgs A) {
       const double hp = hb * 0.5;
       o.axis = axis;
       o.geo = (cb - hp == cb) || (cb + hp == cb) || (hp == 0.0);
-      o.nonfinite = !(isfinite(QK) && isfinite(QG)) || !F::in_range(P, c, h);
+      o.nonfinite = !(isfinite(QK) && isfinite(QG)) || !F::in_range_rt(P, D, c, h);
       store_result(A, r, o);
       dd_add(qs, o.q);
       dd_add(es, o.err);

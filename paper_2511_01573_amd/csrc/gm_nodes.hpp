@@ -104,6 +104,15 @@ struct Alg {
       tm = t[1];
     }
   }
+  // The centre factor of axis j into tc[j] (a rotation's is 1 and has no place there).
+  __device__ static __forceinline__ void centre(const DevParams& P, int j, double c, T* tc) {
+    if constexpr (!kUnitCentre) {
+      const double x[1] = {c};
+      T t[1];
+      terms<1>(P, j, x, t);
+      tc[j] = t[0];
+    }
+  }
   // The rotation family's base e^{i (c0 + sum a_j c_j)}: the angle is summed in
   // double-double, so it carries no rounding of its own.
   template <int D>

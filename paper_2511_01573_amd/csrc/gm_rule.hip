@@ -193,7 +193,7 @@ void rule_tpr_kernel(RuleArgs A) {
   for (; v < end; v += stride) {
     const int64_t r = pairs ? ((v & 1) ? R.nkeep + (v >> 1) : (v >> 1)) : v;
     double c[D], h[D];
-    const int lvl = load_active<D, 1>(R, r, 0, c, h);
+    const int lvl = load_active<D>(R, r, c, h);
     double volo;
     const DevParams& P = region_params<BATCH>(A, buf, r, volo);
     const double vol = ldexp(volo, -lvl);
@@ -240,35 +240,21 @@ __global__ __launch_bounds__(kRuleBlock) void rule_wpr_kernel(RuleArgs A) {
     const bool valid = r < n;
     double volo;
     const DevParams& P = region_params<BATCH>(A, buf, valid ? r : start, volo);
-    double c[D], h[D];
-    int lvl = 0;
-    if (valid) {
-      lvl = load_active<D, L>(R, r, s, c, h);
-    } else {
-#pragma unroll
-      for (int j = 0; j < D; ++j) {
-        c[j] = 0.5;
-        h[j] = 0.25;
-      }
-    }
-    // Per-region tables (each lane of the group writes the coordinates j = s mod L).
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-      if ((j & (L - 1)) == s) {
-        sl.c[j] = c[j];
-        sl.h[j] = h[j];
-      }
-    }
+    // Per-region tables, the axes dealt out to the lanes.
+    const int lvl = load_axes<D, L>(R, valid, r, valid ? list_entry(R, r) : 0, s,
+                                    [&](int j, double c, double h) {
+                                      sl.c[j] = c;
+                                      sl.h[j] = h;
+                                      sl.tc[j] = F::term(P, j, c);
+                                    });
+    wave_lds_sync();
     double tc[D];
 #pragma unroll
-    for (int j = 0; j < D; ++j) tc[j] = F::term(P, j, c[j]);
+    for (int j = 0; j < D; ++j) tc[j] = sl.tc[j];
     double pc = 0.0, full = 0.0;
 #pragma unroll
     for (int k = 0; k < D; ++k) {
-      if ((k & (L - 1)) == s) {
-        sl.tc[k] = tc[k];
-        sl.pc[k] = pc;
-      }
+      if ((k & (L - 1)) == s) sl.pc[k] = pc;
       pc = (k == 0) ? tc[0] : F::comb(pc, tc[k]);
     }
     full = pc;
@@ -340,8 +326,9 @@ __global__ __launch_bounds__(kRuleBlock) void rule_wpr_kernel(RuleArgs A) {
       double t5p[D], t5m[D];
 #pragma unroll
       for (int j = 0; j < D; ++j) {
-        t5p[j] = F::term(P, j, fma(K.lam5, h[j], c[j]));
-        t5m[j] = F::term(P, j, fma(-K.lam5, h[j], c[j]));
+        const double c = sl.c[j], h = sl.h[j];
+        t5p[j] = F::term(P, j, fma(K.lam5, h, c));
+        t5m[j] = F::term(P, j, fma(-K.lam5, h, c));
       }
       corner_sweep<D, FAM, LOG2L>(P, t5p, t5m, (uint32_t)s, S5);
     }

@@ -52,9 +52,9 @@ __device__ __forceinline__ void chain_n(double (&x)[N], const double* tc, int k0
   }
 }
 
-// Three wavefronts per SIMD up to d = 10 (at most a few values spill to
-// scratch, and the extra wavefront hides more latency); two above, where the
-// spill would grow.
+// Three wavefronts per SIMD up to d = 10 (the oscillatory family's cosine spills up
+// to 58 registers there, the others at most 4); two above, where all but it stay
+// below 190.
 template <int D, int FAM, int LOG2L, bool BATCH>
 __global__ __launch_bounds__(kRuleBlock) __attribute__((amdgpu_waves_per_eu(D <= 10 ? 3 : 2)))
 void rule9_kernel(RuleArgs A) {
@@ -87,41 +87,24 @@ void rule9_kernel(RuleArgs A) {
     const bool valid = r < n;
     double volo;
     const DevParams& P = region_params<BATCH>(A, buf, valid ? r : start, volo);
-    double c[D], h[D];
-    int lvl = 0;
-    if (valid) {
-      lvl = load_listed<D, L>(R, r, entry, s, c, h);
-    } else {
-#pragma unroll
-      for (int j = 0; j < D; ++j) {
-        c[j] = 0.5;
-        h[j] = 0.25;
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-      if ((j & (L - 1)) == s) {
-        sl.c[j] = c[j];
-        sl.h[j] = h[j];
-      }
-    }
-    double tc[D];
-#pragma unroll
-    for (int j = 0; j < D; ++j) tc[j] = F::term(P, j, c[j]);
+    const int lvl = load_axes<D, L>(R, valid, r, entry, s, [&](int j, double c, double h) {
+      sl.c[j] = c;
+      sl.h[j] = h;
+      sl.tc[j] = F::term(P, j, c);
+      sl.tp[0][j] = F::term(P, j, fma(K.lam2, h, c));
+      sl.tp[1][j] = F::term(P, j, fma(-K.lam2, h, c));
+      sl.tp[2][j] = F::term(P, j, fma(K.lam3, h, c));
+      sl.tp[3][j] = F::term(P, j, fma(-K.lam3, h, c));
+      sl.tp[4][j] = F::term(P, j, fma(K.lam6, h, c));
+      sl.tp[5][j] = F::term(P, j, fma(-K.lam6, h, c));
+    });
+    wave_lds_sync();
     double pc = 0.0;
 #pragma unroll
     for (int k = 0; k < D; ++k) {
-      if ((k & (L - 1)) == s) {
-        sl.tc[k] = tc[k];
-        sl.pc[k] = pc;
-        sl.tp[0][k] = F::term(P, k, fma(K.lam2, h[k], c[k]));
-        sl.tp[1][k] = F::term(P, k, fma(-K.lam2, h[k], c[k]));
-        sl.tp[2][k] = F::term(P, k, fma(K.lam3, h[k], c[k]));
-        sl.tp[3][k] = F::term(P, k, fma(-K.lam3, h[k], c[k]));
-        sl.tp[4][k] = F::term(P, k, fma(K.lam6, h[k], c[k]));
-        sl.tp[5][k] = F::term(P, k, fma(-K.lam6, h[k], c[k]));
-      }
-      pc = (k == 0) ? tc[0] : F::comb(pc, tc[k]);
+      const double tc = sl.tc[k];
+      if ((k & (L - 1)) == s) sl.pc[k] = pc;
+      pc = (k == 0) ? tc : F::comb(pc, tc);
     }
     __syncthreads();
     const double f0 = F::template outer<D>(P, pc);
@@ -209,8 +192,9 @@ void rule9_kernel(RuleArgs A) {
       double t5p[D], t5m[D];
 #pragma unroll
       for (int j = 0; j < D; ++j) {
-        t5p[j] = F::term(P, j, fma(K.lam5, h[j], c[j]));
-        t5m[j] = F::term(P, j, fma(-K.lam5, h[j], c[j]));
+        const double c = sl.c[j], h = sl.h[j];
+        t5p[j] = F::term(P, j, fma(K.lam5, h, c));
+        t5m[j] = F::term(P, j, fma(-K.lam5, h, c));
       }
       corner_sweep<D, FAM, LOG2L>(P, t5p, t5m, (uint32_t)s, S5);
     }
