@@ -113,14 +113,15 @@ int hipLaunchKernel(const void*, Dim, Dim, void** args, size_t, void*) {
   const int64_t stop = g_stop_at < 0 ? -g_stop_at : g_stop_at;
   if (g_iter < stop && g_launches > 1 && (g_launches - 2) % per == 1) {
     const Mirror* m = (const Mirror*)args[6];
+    int64_t* w = *(int64_t**)args[0];  // the status block
     ++g_iter;
+    w[0] = 20000;            // n_active
+    w[1] = 20000;            // n_prev
+    w[3] = g_iter;           // iter
+    w[4] = g_iter >= stop;   // done
+    w[11] = 15000 * g_iter;  // leaf_count
     if (m->slot) {
-      int64_t* w = m->slot->words;
-      w[0] = 20000;             // n_active
-      w[1] = 20000;             // n_prev
-      w[3] = g_iter;            // iter
-      w[4] = g_iter >= stop;    // done
-      w[11] = 15000 * g_iter;   // leaf_count
+      std::memcpy(m->slot, w, 8 * g_seq_word);
       ((int64_t*)m->slot)[g_seq_word] = m->seq;
     }
   }
