@@ -28,6 +28,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/gm.h"
@@ -1260,11 +1261,20 @@ static StatusSlot* status_slots(bool create) {
 }
 static int64_t g_status_seq = 0;  // numbers the iterations of every run
 
+// How the process wants HIP to wait (hipDeviceSchedule...): the slots are for one
+// that spins, as HIP does by default.
+static unsigned wait_mode() {
+  unsigned flags = 0;
+  if (hipGetDeviceFlags(&flags) != hipSuccess) (void)hipGetLastError();
+  return flags & hipDeviceScheduleMask;
+}
+
 // Wait until the GPU has filled the slot for iteration number seq.  Ends with
 // an error if the stream drains or fails without it.
-static int await_slot(const StatusSlot* slot, int64_t seq, hipStream_t s, Status* out) {
+static int await_slot(const StatusSlot* slot, int64_t seq, bool yield, hipStream_t s, Status* out) {
   for (int64_t spin = 1;; ++spin) {
     if (__atomic_load_n(&slot->seq, __ATOMIC_ACQUIRE) == seq) break;
+    if (yield) std::this_thread::yield();
     if ((spin & 0x3fff) == 0) {
       const hipError_t e = hipStreamQuery(s);
       if (e == hipSuccess && __atomic_load_n(&slot->seq, __ATOMIC_ACQUIRE) != seq) {
@@ -1436,7 +1446,8 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
   // at most one is launched in vain.  Gradient mode keeps one (the leaf store
   // grows on the host's side).  Without slots (none made before a call on the
   // no-allocation path) the host launches a few iterations and copies the status
-  // behind them: 6 below 2^16 active regions, 3 below 2^20, 2 above.
+  // behind them: 6 below 2^16 active regions, 3 below 2^20, 2 above; and so it does
+  // in a process that asked HIP to block while it waits.
   //
   // How many are in flight decides neither the kernels nor a bit of the result:
   // with more than one, iteration k takes the rule-kernel mapping of twice
@@ -1451,6 +1462,8 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
     for (auto& row : events.ev)
       for (auto& e : row) GM_HIP(hipEventCreate(&e));
   StatusSlot* const slots = status_slots(fixed_base == nullptr);
+  const unsigned wait = wait_mode();
+  const bool mirrored = slots && wait != hipDeviceScheduleBlockingSync;
 
   const ListFn list_fn = keep_leaves ? leaf_list_fn(d, true) : list_kernel<0, true>;
   int64_t n = n0;             // active regions of iteration `seen`
@@ -1468,7 +1481,7 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
     int ahead = 1;
     if (!keep_leaves) {
       if (g_opt.graph_iters > 0) ahead = std::min(g_opt.graph_iters, kMaxAhead);
-      else if (slots) ahead = 2;
+      else if (mirrored) ahead = 2;
       else ahead = n < (1 << 16) ? 6 : n < (1 << 20) ? 3 : 2;
     } else {
       // Room for every region of this iteration to retire.
@@ -1495,7 +1508,7 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
       hipEvent_t* const e = events.ev[launched % kMaxAhead];
       const int64_t seq = ++g_status_seq;
       const bool copied = keep_leaves && launched == 0;
-      const Mirror mir{slots && !copied ? slots + seq % kSlots : nullptr, seq};
+      const Mirror mir{mirrored && !copied ? slots + seq % kSlots : nullptr, seq};
       if (timing) GM_HIP(hipEventRecord(e[0], s));
       GM_HIP(launch_rule(d, kfam, map, ra, rg, s));
       if (timing) GM_HIP(hipEventRecord(e[1], s));
@@ -1536,9 +1549,9 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
       nb = std::min<int64_t>(cap, 2 * nb);
     }
     const int64_t before = seen;
-    if (slots && !(keep_leaves && seen == 0)) {
+    if (mirrored && !(keep_leaves && seen == 0)) {
       const int64_t seq = seq0 + seen + 1;
-      rc = await_slot(slots + seq % kSlots, seq, s, &hst);
+      rc = await_slot(slots + seq % kSlots, seq, wait == hipDeviceScheduleYield, s, &hst);
       if (rc != GM_OK) return rc;
       seen += 1;
     } else {
@@ -1583,7 +1596,7 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
   }
   // (an iteration launched in vain returns at once, but is part of this call)
   drain.owed = false;
-  if (slots) GM_HIP(hipStreamSynchronize(s));
+  if (mirrored) GM_HIP(hipStreamSynchronize(s));
 
   out->I = hst.I;
   out->E = hst.E;
