@@ -1106,28 +1106,37 @@ static int forced_log2l() {
 // common work, so the one-lane kernel wins from fewer on.  Corner peak (quotient
 // form) at d = 8, us for 1 / 4 / 16 lanes: n = 8192: 19 / 18 / 19, 32768: 20 / 27 /
 // 45, 65536: 23 / 40 / 78; d = 10: n = 32768: 47 / 41 / 60, 65536: 56 / 70 / 106.
-// Factored, d = 13 product peak, 1 / 4 / 16 / 64 lanes: n = 1024: 38 / 29 / 30 /
-// 24, 4096: 42 / 28 / 23 / 37, 16384: 43 / 29 / 38 / 91, 65536: 46 / 77 / 132 /
-// 345; up to d = 10 one lane is the fastest at every n (d = 8 Gaussian, n = 256:
-// 11 / 15 / 19 us, 49166: 18 / 30 / 65).
+// Factored, 1 / 4 / 16 / 64 lanes, product peak, d = 11: n = 4096: 18 / 18 / 13 /
+// 19, 16384: 17 / 19 / 21 / 51, 65536: 22 / 42 / 61 / 180; d = 13: n = 1: 39 / 24 /
+// 13 / 12, 8192: 35 / 26 / 18 / 32, 32768: 39 / 37 / 46 / 107, 65536: 42 / 67 / 81 /
+// 208; d = 16, where the one-lane kernel spills 100 registers: n = 64: 198 / 71 / 27
+// / 17, 65536: 206 / 275 / 253 / 428, 262144: 733 / 1057 / 997 / 1430 (oscillatory,
+// Gaussian and C0 cross at the same sizes; at d = 11 one lane is ahead from 32768 on
+// already, 18 / 24).  Up to d = 10 one lane is the fastest at every n (d = 8
+// Gaussian, n = 256: 11 / 15 / 19 us, 49166: 18 / 30 / 65).
 constexpr int64_t kTargetLanes = 131072;
 static int64_t target_lanes(int d, bool factored) {
   if (factored) return d <= kTprMaxDim ? 0 : 65536;
   return d < 10 ? 32768 : d == 10 ? 65536 : kTargetLanes;
 }
 // Active sets from which the factored degree-9 rule runs one lane per region: at
-// every size up to d = 9 (d = 8 Gaussian, one lane against the several it
-// replaces, n = 256: 16 / 21 us, 4096: 17 / 33, 65536: 20 / 73); at d = 10 the
-// 64-lane kernel is ahead in small sets (n = 1024: 30 / 21, 4096: 32 / 35).
-constexpr int64_t r9_tpr_regions(int d) { return d < 10 ? 0 : 4096; }
+// every size up to d = 8 (Gaussian, one lane against the several of the chain form,
+// n = 256: 16 / 17 us, 3684: 20 / 30, 22090: 18 / 41); above, the 64-lane kernel is
+// ahead in small sets (one / 64 lanes, d = 9 C0, n = 1024: 26 / 13, 4096: 25 / 21,
+// 8192: 25 / 34; d = 10, n = 1024: 31 / 14, 4096: 32 / 23, 8192: 31 / 35; the
+// rotations cross at the same sizes).
+constexpr int64_t r9_tpr_regions(int d) {
+  return d < kFactor9WideMinDim ? 0 : d == 9 ? 5120 : 6144;
+}
 
 int choose_mapping(int d, int kfam, int64_t n, bool list) {
   const bool factored = is_factored(kfam);
   if (g_opt.rule == 1) return kMapGk;
   if (g_opt.rule == 2) {
     if (factored && d <= kTprMaxDim && n >= r9_tpr_regions(d)) return kMapR9Tpr;
-    // the wide mapping while the default one would leave the GPU mostly idle
-    const bool wide = (n << rule9_log2l(d)) < kTargetLanes;
+    // the wide mapping while the default one would leave the GPU mostly idle (the
+    // factored several-lane kernels have no other)
+    const bool wide = factored || (n << rule9_log2l(d)) < kTargetLanes;
     return kMapR9 + (wide ? rule9_log2l_wide(d) : rule9_log2l(d));
   }
   const bool tpr = d <= kTprMaxDim || factored;

@@ -548,8 +548,9 @@ RuleKernelFn rule9_kernel_f5(int d, bool batch, bool wide);
 RuleKernelFn rule9_kernel_f6(int d, bool batch, bool wide);
 RuleKernelFn rule9_kernel_f7(int d, bool batch, bool wide);
 // The same for the factored kernel families (single store only): one lane per
-// region (log2l < 0, d <= kTprMaxDim), rule9_log2l_wide(d) (d >= kTprMaxDim) or
-// rule9_log2l(d) (d > kTprMaxDim).
+// region (log2l < 0, d <= kTprMaxDim) or rule9_log2l_wide(d) (d >=
+// kFactor9WideMinDim).
+constexpr int kFactor9WideMinDim = 9;
 RuleKernelFn factor9_kernel_f8(int d, int log2l);
 RuleKernelFn factor9_kernel_f9(int d, int log2l);
 RuleKernelFn factor9_kernel_f10(int d, int log2l);

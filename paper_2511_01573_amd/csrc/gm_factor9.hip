@@ -9,9 +9,9 @@
 // unmoved ones.  About 3150 FP64 operations a region at d = 8, 1200 of them the
 // factors: d = 8 C0, 1.0e6 regions: 130 us (7.5e9 regions/s, 24 TFLOP/s; the
 // chain kernel's eight lanes per region: 1100 us).  Above d = 10, and in small
-// sets at d = 10, L lanes of one wavefront per region as in gm_rule9.hip: the region's factors, and the products of its centre factors before an axis,
-// after it and strictly between two, are formed by its lanes together in LDS,
-// so a node of an axis pair or triple (77% of the 1089 nodes at d = 8) is two
+// sets at d = 9 and 10, the 64 lanes of a wavefront per region as in gm_rule9.hip:
+// the region's factors, and the products of its centre factors before an axis, after
+// it and strictly between two, are formed by its lanes together in LDS, so a node of an axis pair or triple (77% of the 1089 nodes at d = 8) is two
 // to four multiplications of shared products instead of an exponential behind a
 // chain over the axes that it does not move.
 #include "gm_nodes.hpp"
@@ -32,7 +32,7 @@ struct Factor9Slot {
   double c[D], h[D], dv[D], sc[D];
 };
 
-// Three wavefronts per SIMD at d = 10 (the rotation family spills 16 registers
+// Three wavefronts per SIMD up to d = 10 (the rotation family spills 16 registers
 // there); two above, where the compiler uses 128 to 200 registers (rotations: 200 to
 // 256, with up to 18 spilled from d = 14 on).
 template <int D, int FAM, int LOG2L>
@@ -355,10 +355,7 @@ static RuleKernelFn f9_pick(int log2l) {
   if constexpr (D <= kTprMaxDim) {
     if (log2l < 0) return factor9_tpr_kernel<D, F>;
   }
-  if constexpr (D > kTprMaxDim) {
-    if (log2l == rule9_log2l(D)) return factor9_kernel<D, F, rule9_log2l(D)>;
-  }
-  if constexpr (D >= kTprMaxDim) {
+  if constexpr (D >= kFactor9WideMinDim) {
     if (log2l == rule9_log2l_wide(D)) return factor9_kernel<D, F, rule9_log2l_wide(D)>;
   }
   return nullptr;
