@@ -199,7 +199,7 @@ GM_HD void sin_n(const double (&x)[N], double (&y)[N]) {
   }
 }
 
-// sin and cos of x + xl (xl a correction far below x) with the reduction and
+// sin and cos of x + xl (xl a correction, below x / 2^40) with the reduction and
 // polynomials of cos_n and sin_n: x = r + k pi, r = rh + rl.  One reduction
 // serves both.  REDUCED_TAIL = false leaves rl out (for angles that carry a
 // rounding of their own of that size).
@@ -218,7 +218,16 @@ GM_HD void sincos_n(const double (&x)[N], const double (&xl)[N], double (&sn)[N]
 #pragma unroll
   for (int i = 0; i < N; ++i) {
     rh[i] = fma(-kd[i], kPi_2, r1[i]);
-    rl[i] = REDUCED_TAIL ? fma(-kd[i], kPi_3, fma(-kd[i], kPi_2, r1[i] - rh[i])) + xl[i] : 0.0;
+    rl[i] = 0.0;
+    if (REDUCED_TAIL) {
+      // (the correction enters below to first order in a Taylor step, exact enough
+      // for half an ulp of rh only: with xl it can be far more, so the sum is
+      // brought to that form again)
+      const double t = fma(-kd[i], kPi_3, fma(-kd[i], kPi_2, r1[i] - rh[i])) + xl[i];
+      const double r = rh[i] + t, tr = r - rh[i];
+      rl[i] = (rh[i] - (r - tr)) + (t - tr);
+      rh[i] = r;
+    }
   }
 #pragma unroll
   for (int i = 0; i < N; ++i) {
@@ -302,7 +311,11 @@ GM_HD void rcp3_n(const double (&x)[N], double (&y)[N]) {
 #if defined(__HIP_DEVICE_COMPILE__)
     r[i] = __builtin_amdgcn_rcp(x[i]);
 #else
-    r[i] = 1.0 / x[i];
+    r[i] = 1.0 / x[i];  // as coarse as the estimate: the mantissa's first 22 bits
+    uint64_t w;
+    std::memcpy(&w, &r[i], sizeof w);
+    w &= ~((UINT64_C(1) << 30) - 1);
+    std::memcpy(&r[i], &w, sizeof w);
 #endif
   }
 #pragma unroll
