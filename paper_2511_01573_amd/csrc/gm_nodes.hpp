@@ -196,7 +196,8 @@ __device__ __forceinline__ void sign_table(typename Alg<FAM>::T s,
 // 16 entries, kept in registers).  A group's NA running sums of at most eight
 // corners each hide the latency of the accumulation; they are added pairwise,
 // so a corner passes through at most 8 + log2 NA roundings before the
-// compensated sum (the chain form's plain sum of 16 corners: 15).
+// compensated sum, a rotation (two multiply-adds a corner) through 16 + log2 NA (the
+// chain form's plain sum of 16 corners: 15).
 template <int D, int FAM, int LB>
 __device__ __forceinline__ void corner_sum(typename Alg<FAM>::T base,
                                            const typename Alg<FAM>::T (&tp)[D],
@@ -205,6 +206,7 @@ __device__ __forceinline__ void corner_sum(typename Alg<FAM>::T base,
   using F = Alg<FAM>;
   using T = typename F::T;
   constexpr int NC = D - LB;
+  static_assert(NC >= 3, "several lanes only from d = 9 on, 64 at most");
   constexpr int RB = NC >= 8 ? 4 : (NC + 1) / 2;  // last axes, table R
   constexpr int GMAX = F::kUnitCentre ? 3 : 4;    // unrolled axes before them, table G
   constexpr int GB = NC - RB < GMAX ? NC - RB : GMAX;
@@ -216,49 +218,45 @@ __device__ __forceinline__ void corner_sum(typename Alg<FAM>::T base,
     if ((lane_bits >> j) & 1u) t = tm[j];
     pl = (j == 0 && !F::kUnitCentre) ? t : F::comb(pl, t);
   }
-  if constexpr (NC == 0) {
-    ks_add(S5, F::value(pl));  // the lane's one corner
-  } else {
-    constexpr int NR = 1 << RB;
-    constexpr int NA = NR < 8 ? NR : 8;            // running sums
-    constexpr int NG = 1 << GB, GS = NG < 4 ? NG : 4;  // entries of G, and of a group
-    T R[NR];
-    sign_table<D, FAM, D - RB, RB, false>(F::none(), tp, tm, R);
+  constexpr int NR = 1 << RB;
+  constexpr int NA = NR < 8 ? NR : 8;            // running sums
+  constexpr int NG = 1 << GB, GS = NG < 4 ? NG : 4;  // entries of G, and of a group
+  T R[NR];
+  sign_table<D, FAM, D - RB, RB, false>(F::none(), tp, tm, R);
 #pragma unroll 1
-    for (uint32_t m = 0; m < (1u << NO); ++m) {
-      T pre = pl;
+  for (uint32_t m = 0; m < (1u << NO); ++m) {
+    T pre = pl;
 #pragma unroll
-      for (int q = 0; q < NO; ++q) {
-        T t = tp[LB + q];
-        if ((m >> q) & 1u) t = tm[LB + q];
-        pre = (LB + q == 0 && !F::kUnitCentre) ? t : F::comb(pre, t);
-      }
-      T G[NG];
-      sign_table<D, FAM, LB + NO, GB, F::kUnitCentre || LB + NO != 0>(pre, tp, tm, G);
+    for (int q = 0; q < NO; ++q) {
+      T t = tp[LB + q];
+      if ((m >> q) & 1u) t = tm[LB + q];
+      pre = (LB + q == 0 && !F::kUnitCentre) ? t : F::comb(pre, t);
+    }
+    T G[NG];
+    sign_table<D, FAM, LB + NO, GB, F::kUnitCentre || LB + NO != 0>(pre, tp, tm, G);
 #pragma unroll
-      for (int g0 = 0; g0 < NG; g0 += GS) {
-        double acc[NA];
+    for (int g0 = 0; g0 < NG; g0 += GS) {
+      double acc[NA];
 #pragma unroll
-        for (int g = 0; g < GS; ++g) {
-          T a[NA];
+      for (int g = 0; g < GS; ++g) {
+        T a[NA];
 #pragma unroll
-          for (int q = 0; q < NA; ++q) a[q] = G[g0 + g];
+        for (int q = 0; q < NA; ++q) a[q] = G[g0 + g];
 #pragma unroll
-          for (int k = 0; k < NR; k += NA) {
-            T b[NA];
+        for (int k = 0; k < NR; k += NA) {
+          T b[NA];
 #pragma unroll
-            for (int q = 0; q < NA; ++q) b[q] = R[k + q];
-            if (g == 0 && k == 0) F::template accumulate<NA, true>(a, b, acc);
-            else F::template accumulate<NA, false>(a, b, acc);
-          }
+          for (int q = 0; q < NA; ++q) b[q] = R[k + q];
+          if (g == 0 && k == 0) F::template accumulate<NA, true>(a, b, acc);
+          else F::template accumulate<NA, false>(a, b, acc);
         }
-#pragma unroll
-        for (int w = NA / 2; w >= 1; w >>= 1) {
-#pragma unroll
-          for (int q = 0; q < w; ++q) acc[q] = acc[q] + acc[q + w];
-        }
-        ks_add(S5, acc[0]);
       }
+#pragma unroll
+      for (int w = NA / 2; w >= 1; w >>= 1) {
+#pragma unroll
+        for (int q = 0; q < w; ++q) acc[q] = acc[q] + acc[q + w];
+      }
+      ks_add(S5, acc[0]);
     }
   }
 }
