@@ -1478,12 +1478,13 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
   int64_t n = n0;             // active regions of iteration `seen`
   int64_t n_before = 0;       // ... and of the one before it
   int64_t leaves_have = 0;
-  // A gradient's first iteration, with which the tiny ones end: its status is copied to
-  // pinned memory (where nothing runs meanwhile that is sooner there than the slot
-  // behind its fence), and its leaf list, which a run that ends there has not, waits
-  // for it (d = 2, one iteration: 85 -> 64 us; with copies throughout, gradients of 7
-  // iterations 270 -> 305).
-  bool list_due = false;
+  // A gradient's first iteration, with which the tiny ones end, copies its status to
+  // pinned memory: with one iteration in flight nothing runs meanwhile, and that is
+  // there sooner than the slot behind its fence.  Geometric means over small
+  // gradients, us, with a slot / with the copy, of one iteration 87 / 73, two 108 /
+  // 111, three 151 / 146; with copies throughout, seven take 305 instead of 270.
+  // (Its leaf list launched behind the copy, which spares a run that ends there the
+  // launch: 71, 117, 145.)
   int64_t seen = 0, launched = 0;  // iterations whose status is known / launched
   const int64_t seq0 = g_status_seq;
   for (;;) {
@@ -1526,12 +1527,9 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
                            la, toff, mir);
         GM_HIP(hipGetLastError());
         if (keep_leaves) {
-          list_due = launched == 0;
-          if (!list_due) {
-            hipLaunchKernelGGL(leaf_list_fn(d, false), dim3(tg), dim3(kTileThreads), 0, s, la,
-                               Mirror{});
-            GM_HIP(hipGetLastError());
-          }
+          hipLaunchKernelGGL(leaf_list_fn(d, false), dim3(tg), dim3(kTileThreads), 0, s, la,
+                             Mirror{});
+          GM_HIP(hipGetLastError());
         }
         nb = std::min<int64_t>(cap, 2 * nb);
         continue;
@@ -1594,12 +1592,6 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
                    (long long)hst.done);
     leaves_have = hst.leaf_count;
     if (hst.done) break;
-    if (list_due) {
-      hipLaunchKernelGGL(leaf_list_fn(d, false), dim3(tile_grid_for(n0)), dim3(kTileThreads), 0, s,
-                         la, Mirror{});
-      GM_HIP(hipGetLastError());
-      list_due = false;
-    }
     n = hst.n_active;
     n_before = hst.n_prev;
   }
