@@ -1478,13 +1478,6 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
   int64_t n = n0;             // active regions of iteration `seen`
   int64_t n_before = 0;       // ... and of the one before it
   int64_t leaves_have = 0;
-  // A gradient's first iteration, with which the tiny ones end, copies its status to
-  // pinned memory: with one iteration in flight nothing runs meanwhile, and that is
-  // there sooner than the slot behind its fence.  Geometric means over small
-  // gradients, us, with a slot / with the copy, of one iteration 87 / 73, two 108 /
-  // 111, three 151 / 146; with copies throughout, seven take 305 instead of 270.
-  // (Its leaf list launched behind the copy, which spares a run that ends there the
-  // launch: 71, 117, 145.)
   int64_t seen = 0, launched = 0;  // iterations whose status is known / launched
   const int64_t seq0 = g_status_seq;
   for (;;) {
@@ -1517,8 +1510,7 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
       g_stats.lanes_per_region = lanes_of_mapping(map, d);
       hipEvent_t* const e = events.ev[launched % kMaxAhead];
       const int64_t seq = ++g_status_seq;
-      const bool copied = keep_leaves && launched == 0;
-      const Mirror mir{mirrored && !copied ? slots + seq % kSlots : nullptr, seq};
+      const Mirror mir{mirrored ? slots + seq % kSlots : nullptr, seq};
       if (timing) GM_HIP(hipEventRecord(e[0], s));
       GM_HIP(launch_rule(d, kfam, map, ra, rg, s));
       if (timing) GM_HIP(hipEventRecord(e[1], s));
@@ -1556,8 +1548,14 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
       nb = std::min<int64_t>(cap, 2 * nb);
     }
     const int64_t before = seen;
-    if (mirrored && !(keep_leaves && seen == 0)) {
+    if (mirrored) {
       const int64_t seq = seq0 + seen + 1;
+      // A gradient's first iteration, with which the tiny ones end: with one in
+      // flight nothing runs meanwhile, and the stream's wait, which the call owes at
+      // its end anyway, costs less here than after a loop on the slot (gradients of
+      // one iteration: 83 -> 65 us, of several the same; a copy of the status in its
+      // place slows the launches after it, 12 iterations 433 -> 457).
+      if (keep_leaves && seen == 0) GM_HIP(hipStreamSynchronize(s));
       rc = await_slot(slots + seq % kSlots, seq, wait == hipDeviceScheduleYield, s, &hst);
       if (rc != GM_OK) return rc;
       seen += 1;
@@ -1595,9 +1593,10 @@ int run_adaptive(int fam, const double* params, int d, const double* lo, const d
     n = hst.n_active;
     n_before = hst.n_prev;
   }
-  // (an iteration launched in vain returns at once, but is part of this call)
+  // (an iteration launched in vain returns at once, but is part of this call; the
+  // adjoint kernels of gradient mode, which has none, follow on the stream)
   drain.owed = false;
-  if (mirrored) GM_HIP(hipStreamSynchronize(s));
+  if (mirrored && !keep_leaves) GM_HIP(hipStreamSynchronize(s));
 
   out->I = hst.I;
   out->E = hst.E;

@@ -103,8 +103,10 @@ extern "C" int gm_integrate_grad(int integrand_id, const double* params, int d, 
   std::lock_guard<std::mutex> lk(api_mutex());
   hipStream_t s = (hipStream_t)stream;
   RunResult rr;
-  rc = check_bounds(
-      run_adaptive(integrand_id, params, d, lo, hi, rel_tol, abs_tol, max_regions, s, true, &rr));
+  DrainOnError drain{s, false};
+  rc = run_adaptive(integrand_id, params, d, lo, hi, rel_tol, abs_tol, max_regions, s, true, &rr);
+  drain.owed = rc == GM_OK;  // (the run's last kernel may still be at work)
+  rc = check_bounds(rc);
   if (rc != GM_OK) return rc;
   if (rr.status == GM_NONFINITE) {
     *out_est = rr.I;
@@ -149,7 +151,6 @@ extern "C" int gm_integrate_grad(int integrand_id, const double* params, int d, 
     active.cap = rr.cap;
     active.npar = rr.final_npar;
     active.split = rr.final_split;
-    DrainOnError drain{s};
     int64_t blk = 0;
     for (int pt = 0; pt < nparts; ++pt) {
       const AdjFn fn = factored ? factored : adj_fn(d, integrand_id, r9, parts[pt]);

@@ -94,6 +94,8 @@ struct DrainOnError {
 // (the no-allocation entry point's fixed scratch, already checked to be large
 // enough) and the run allocates nothing: no workspace, no pinned status copy
 // (an existing one is used), no timing events.
+// keep_leaves (gradient mode): returns with the last iteration's kernels possibly
+// still at work on s.
 int run_adaptive(int fam, const double* params, int d, const double* lo, const double* hi,
                  double rel_tol, double abs_tol, int64_t max_regions, hipStream_t s,
                  bool keep_leaves, RunResult* out, char* fixed_base = nullptr);
