@@ -745,6 +745,7 @@ int run_batch(int n, const int* fam, const double* params, const int* d, const d
   hb.n_running = nv;
   hb.cap = cap;
   hb.max_iters = opt.max_iters;
+  DrainOnError drain{s};  // (the uploads read this call's arrays)
   auto up = [&](size_t off, const void* src, size_t bytes) {
     return hipMemcpyAsync(base + off, src, bytes, hipMemcpyHostToDevice, s);
   };
@@ -950,6 +951,7 @@ int run_batch(int n, const int* fam, const double* params, const int* d, const d
     }
     if (hb.n_running == 0) break;
   }
+  if (e != hipSuccess) (void)hipStreamSynchronize(s);  // (before its graph goes away)
   if (exec) (void)hipGraphExecDestroy(exec);
   if (graph) (void)hipGraphDestroy(graph);
   if (ev0) (void)hipEventDestroy(ev0);
@@ -958,6 +960,7 @@ int run_batch(int n, const int* fam, const double* params, const int* d, const d
   e = hipMemcpyAsync(items.data(), A.items, sizeof(ItemState) * nv, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return record_hip_error(e);
+  drain.owed = false;
   int worst = GM_OK;
   int64_t evals = 0, regions = 0;
   for (int k = 0; k < nv; ++k) {

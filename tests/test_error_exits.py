@@ -25,12 +25,16 @@ D.double_reset.argtypes = [C.c_int, C.c_int, C.c_int64, C.c_int]
 SEQ = 27  # words of the status block (gm_common.hpp Status), then the number
 out = []
 def call(kind, fail_malloc=0, fail_launch=0, stop=6):
-    stop = {"grad": stop, "integrate": -stop, "regions": 0}[kind]
+    stop = {"grad": stop, "integrate": -stop, "regions": 0, "batch": 0}[kind]
     D.double_reset(fail_malloc, fail_launch, stop, SEQ)
     d, n = 3, 20000
     box = ("gaussian", np.ones(2 * d), np.zeros(d), np.ones(d))
     try:
-        if kind == "regions":
+        if kind == "batch":
+            k = 300
+            gm.integrate_batch(["gaussian"] * k, [box[1]] * k, [d] * k, [box[2]] * k, [box[3]] * k,
+                               [1e-9] * k, [1e-300] * k, 1 << 21, stream=0)
+        elif kind == "regions":
             gm.eval_regions(*box, np.zeros((n, d)), np.ones((n, d)), np.zeros(n), stream=0)
         else:
             fn = gm.integrate_grad if kind == "grad" else gm.integrate
@@ -41,9 +45,12 @@ def call(kind, fail_malloc=0, fail_launch=0, stop=6):
     return [rc, D.double_pending(), D.double_launches(), D.double_events()]
 for k, v in spec["options"].items():
     gm.set_option(k, v)
-out.append(call(spec["call"], stop=2))  # makes workspace, slots and a small leaf store
-out.append(call(spec["call"], **spec["fail"]))
-out.append(call(spec["call"]))
+if spec["call"] == "batch":  # (the double ends no batch)
+    out = [[0, 0], call("batch", **spec["fail"]), [0, 0]]
+else:
+    out.append(call(spec["call"], stop=2))  # makes workspace, slots and a small leaf store
+    out.append(call(spec["call"], **spec["fail"]))
+    out.append(call(spec["call"]))
 print("RESULT " + json.dumps(out))
 """
 
@@ -63,6 +70,8 @@ def double(tmp_path_factory):
     ("integrate", {"fail_launch": 6}, {}, -3),
     ("integrate", {"fail_launch": 7}, {"timing": 1}, -3),
     ("regions", {"fail_launch": 3}, {}, -3),  # the layout of a long list's axes
+    ("batch", {"fail_launch": 5}, {}, -3),
+    ("batch", {"fail_launch": 5}, {"timing": 1}, -3),
 ])
 def test_failed_call_leaves_nothing_running(double, call, fail, options, rc):
     spec = json.dumps({"call": call, "fail": fail, "options": options})
