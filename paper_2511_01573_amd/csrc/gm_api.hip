@@ -844,13 +844,13 @@ Layout make_layout(int d, int64_t cap) {
 }
 
 int acquire_workspace(size_t bytes, char** base) {
+  g_last.valid = false;  // the last run's buffers are written over, or go away
   if (g_ext_ptr) {
     if (bytes > g_ext_bytes) return GM_ENOMEM;
     *base = (char*)g_ext_ptr;
     return GM_OK;
   }
   if (bytes > g_own_bytes) {
-    g_last.valid = false;  // the last run's buffers go away
     if (g_own_ptr) {
       GM_HIP(hipDeviceSynchronize());
       GM_HIP(hipFree(g_own_ptr));
@@ -1695,7 +1695,6 @@ int gm_eval_regions(int integrand_id, const double* params, int d, const double*
   if (lg > INT32_MAX) return GM_ENOMEM;  // (5e11 regions: beyond any memory)
   const Layout lay = make_layout(d, cap);
   char* base = nullptr;
-  g_last.valid = false;  // (before the workspace may move)
   rc = acquire_workspace(lay.total, &base);
   if (rc != GM_OK) return rc;
   RuleArgs ra;
