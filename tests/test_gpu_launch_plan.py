@@ -1,7 +1,8 @@
 """Which kernels a run launches, and so the last bits of its estimate and error,
 follow from the run alone: gm_integrate_noalloc as the first call of a process
-(which has no pinned status slots yet), gm_integrate, the same with "timing", and
-gm_integrate_noalloc afterwards give the same bits.  Dimensions, rules and
+(which has no pinned status slots yet), gm_integrate, the same with "timing",
+gm_integrate_noalloc afterwards, and gm_integrate with two, three and eight iterations
+in flight give the same bits.  Dimensions, rules and
 families with more than one rule-kernel mapping, on sets that grow and shrink
 across the lines between them."""
 from __future__ import annotations
@@ -29,9 +30,11 @@ gm.set_option("graph_iters", flight)
 p = W.family_params(fam, d, seed=40 + d)
 lo, hi = W.unit_box(d)
 out = []
-for call in ("noalloc", "integrate", "timing", "noalloc"):
+for call in ("noalloc", "integrate", "timing", "noalloc", 2, 3, 8):
     print("call", call, flush=True)
     gm.set_option("timing", call == "timing")
+    if call in (2, 3, 8):  # as many in flight
+        gm.set_option("graph_iters", call)
     fn = gm.integrate_noalloc if call == "noalloc" else gm.integrate
     I, E, st = fn(fam, p, lo, hi, tau, 1e-16, 1 << log2cap)
     s = gm.last_stats()
@@ -63,5 +66,7 @@ def test_first_call_of_a_process(fam, d, rule, tau, log2cap, init, flight):
     assert r.returncode == 0, (r.stdout[-500:], r.stderr[-1500:])
     first, *rest = json.loads(r.stdout.split("RESULT ")[1])
     print(first[:6], flush=True)
-    for name, got in zip(("gm_integrate", "gm_integrate with timing", "a second noalloc"), rest):
+    assert len(rest) == 6
+    for name, got in zip(("gm_integrate", "gm_integrate with timing", "a second noalloc", "two in flight",
+                          "three", "eight"), rest):
         assert got == first, (name, got[:6], first[:6])
